@@ -1,7 +1,8 @@
 // Correctly rounded FP64 log1p, expm1 and log for the FP64 tracking path.
 //
-// Each function returns the double nearest to the exact function value.  A
-// quick phase evaluates the function as a double-double with a relative error
+// Each function returns the double nearest to the exact function value.  A lean
+// phase (below) decides nearly every argument of the tracking kernels; what it leaves
+// goes to a quick phase, which evaluates the function as a double-double with a relative error
 // below 2^-68 and applies a rounding test (Ziv's strategy): if every real number
 // within that error of the double-double rounds to the same double, that double
 // is the correctly rounded result.  Otherwise an accurate phase (error below
@@ -40,37 +41,33 @@
 
 namespace ptcr {
 
-// Table access.  In device code the tables of the quick phase live in LDS (copied once
-// per workgroup by lds_tables_init): an LDS read is short and is counted apart from
-// global memory loads, so the tables never make a wave wait for an outstanding gather.
+// Table access.  In device code the tables that every evaluation reads -- the lean phase's
+// logarithm cells and 2^(j/128) -- live in LDS (8 KB, copied once per workgroup by
+// lds_tables_init): an LDS read is short and is counted apart from global memory loads, so the
+// tables never make a wave wait for an outstanding gather.  The tables of the quick and accurate
+// logarithm are read from memory: about one evaluation in 10^4 comes to them.
 #if defined(__HIP_DEVICE_COMPILE__)
-__shared__ double lds_log_c[PT_CR_LOG_J1 - PT_CR_LOG_J0 + 1];
-__shared__ double lds_log_l[PT_CR_LOG_J1 - PT_CR_LOG_J0 + 1][2];
-__shared__ double lds_exp_t[128][2];
-#define PT_CR_LOGC(i) (::ptcr::lds_log_c[(i)])
-#define PT_CR_LOGL(i, h) (::ptcr::lds_log_l[(i)][(h)])
-#define PT_CR_EXPT(i, h) (::ptcr::lds_exp_t[(i)][(h)])
+__shared__ double lds_lean_c[256];
+__shared__ double2 lds_lean_l[256];
+__shared__ double2 lds_exp_t[128];
+#define PT_CR_EXPT(i, h) ((h) ? ::ptcr::lds_exp_t[(i)].y : ::ptcr::lds_exp_t[(i)].x)
 #else
-#define PT_CR_LOGC(i) (PT_CR_LOG_C[(i)])
-#define PT_CR_LOGL(i, h) (PT_CR_LOG_L[(i)][(h)])
 #define PT_CR_EXPT(i, h) (PT_CR_EXP_T[(i)][(h)])
 #endif
+#define PT_CR_LOGC(i) (PT_CR_LOG_C[(i)])
+#define PT_CR_LOGL(i, h) (PT_CR_LOG_L[(i)][(h)])
 
 #ifdef __HIPCC__
-// Copy the quick-phase tables into this workgroup's LDS; the caller synchronises the
-// workgroup before the first evaluation.
+// Copy the tables into this workgroup's LDS; the caller synchronises the workgroup before the
+// first evaluation.
 __device__ inline void lds_tables_init() {
 #if defined(__HIP_DEVICE_COMPILE__)
-    const int n = PT_CR_LOG_J1 - PT_CR_LOG_J0 + 1;
-    for (int q = threadIdx.x; q < n; q += blockDim.x) {
-        lds_log_c[q] = PT_CR_LOG_C[q];
-        lds_log_l[q][0] = PT_CR_LOG_L[q][0];
-        lds_log_l[q][1] = PT_CR_LOG_L[q][1];
+    for (int q = threadIdx.x; q < 256; q += blockDim.x) {
+        lds_lean_c[q] = PT_CR_LEAN_LOG[q][0];
+        lds_lean_l[q] = make_double2(PT_CR_LEAN_LOG[q][1], PT_CR_LEAN_LOG[q][2]);
     }
-    for (int q = threadIdx.x; q < 128; q += blockDim.x) {
-        lds_exp_t[q][0] = PT_CR_EXP_T[q][0];
-        lds_exp_t[q][1] = PT_CR_EXP_T[q][1];
-    }
+    for (int q = threadIdx.x; q < 128; q += blockDim.x)
+        lds_exp_t[q] = make_double2(PT_CR_EXP_T[q][0], PT_CR_EXP_T[q][1]);
 #endif
 }
 #endif
@@ -78,6 +75,25 @@ __device__ inline void lds_tables_init() {
 struct dd {
     double h, l;
 };
+
+// Constants of the quick and accurate phases, read from memory where they are used: as literals
+// the compiler keeps them in registers across the whole tracking loop (they are loop-invariant),
+// and spills the loop's own values for them.
+PT_CR_TABLE double PT_CR_COLD_C[21] = {
+    -0x1.999999999999ap-4, 0x1.c71c71c71c71cp-4, -0x1.0000000000000p-3, 0x1.2492492492492p-3,    // -1/10, 1/9, -1/8, 1/7,
+    -0x1.5555555555555p-3, 0x1.999999999999ap-3, -0x1.0000000000000p-2, 0x1.5555555555555p-2,    // -1/6, 1/5, -1/4, 1/3
+    0x1.a01a01a01a01ap-16, 0x1.a01a01a01a01ap-13, 0x1.6c16c16c16c17p-10, 0x1.1111111111111p-7,   // 1/8!, 1/7!, 1/6!, 1/5!,
+    0x1.5555555555555p-5, 0x1.5555555555555p-3,                                                  // 1/4!, 1/3!
+    PT_CR_LN2_H, PT_CR_LN2_L, PT_CR_LN2_128_1, PT_CR_LN2_128_2, PT_CR_LN2_128_3, PT_CR_INV_LN2_128, PT_CR_SQRT2};
+enum { COLD_LOG = 0, COLD_EXP = 8, COLD_LN2 = 14, COLD_LN2_128 = 16, COLD_INV = 19, COLD_SQRT2 = 20 };
+
+PT_CR_HD const double* cold_consts() {
+    const double* c = PT_CR_COLD_C;
+#if defined(__HIP_DEVICE_COMPILE__) && defined(__OPTIMIZE__)
+    asm volatile("" : "+s"(c));   // opaque: loaded here, not hoisted
+#endif
+    return c;
+}
 
 PT_CR_HD dd two_sum(double a, double b) {
     const double s = a + b;
@@ -222,11 +238,12 @@ struct LogRed {
 
 // y = yh + yl > 0 (yh normal or subnormal, |yl| <= ulp(yh)).
 PT_CR_HD LogRed log_reduce(double yh, double yl) {
+    const double* C = cold_consts();
     int e;
     double m = frexp(yh, &e);   // m in [1/2, 1)
     m *= 2.0;
     e -= 1;                     // m in [1, 2)
-    if (m > PT_CR_SQRT2) {
+    if (m > C[COLD_SQRT2]) {
         m *= 0.5;
         e += 1;
     }
@@ -241,11 +258,12 @@ PT_CR_HD LogRed log_reduce(double yh, double yl) {
 
 // Same reduction with the correction term carried exactly (accurate phase).
 PT_CR_HD LogRed log_reduce_accurate(double yh, double yl) {
+    const double* C = cold_consts();
     int e;
     double m = frexp(yh, &e);
     m *= 2.0;
     e -= 1;
-    if (m > PT_CR_SQRT2) {
+    if (m > C[COLD_SQRT2]) {
         m *= 0.5;
         e += 1;
     }
@@ -259,17 +277,19 @@ PT_CR_HD LogRed log_reduce_accurate(double yh, double yl) {
 }
 
 PT_CR_HD dd log_sum_accurate(const LogRed& R, dd p) {
+    const double* C = cold_consts();
     const double kd = (double)R.k;
-    dd kl = two_prod(kd, PT_CR_LN2_H);
-    kl.l = fma(kd, PT_CR_LN2_L, kl.l);
+    dd kl = two_prod(kd, C[COLD_LN2]);
+    kl.l = fma(kd, C[COLD_LN2 + 1], kl.l);
     const dd L = {PT_CR_LOGL(R.j - PT_CR_LOG_J0, 0), PT_CR_LOGL(R.j - PT_CR_LOG_J0, 1)};
     return dd_add(kl, dd_add(L, p));
 }
 
 PT_CR_HD dd log_sum(const LogRed& R, dd p) {
+    const double* C = cold_consts();
     const double kd = (double)R.k;
-    dd kl = two_prod(kd, PT_CR_LN2_H);
-    kl.l = fma(kd, PT_CR_LN2_L, kl.l);
+    dd kl = two_prod(kd, C[COLD_LN2]);
+    kl.l = fma(kd, C[COLD_LN2 + 1], kl.l);
     const dd L = {PT_CR_LOGL(R.j - PT_CR_LOG_J0, 0), PT_CR_LOGL(R.j - PT_CR_LOG_J0, 1)};
     // |L + p| >= |p|/2 (L = ln(m_j), p = ln(m/m_j), same sign or |p| < |L|/2 within a bin),
     // and k ln2 dominates L + p whenever k != 0
@@ -284,14 +304,15 @@ PT_CR_HD dd log_sum(const LogRed& R, dd p) {
 // 2^-18.5 |r| and are evaluated in double.
 PT_CR_HD dd log1p_series_quick(dd r) {
     const double x = r.h;
-    double T = -0x1.999999999999ap-4;                 // -1/10
-    T = fma(x, T, 0x1.c71c71c71c71cp-4);              //  1/9
-    T = fma(x, T, -0x1.0000000000000p-3);             // -1/8
-    T = fma(x, T, 0x1.2492492492492p-3);              //  1/7
-    T = fma(x, T, -0x1.5555555555555p-3);             // -1/6
-    T = fma(x, T, 0x1.999999999999ap-3);              //  1/5
-    T = fma(x, T, -0x1.0000000000000p-2);             // -1/4
-    T = fma(x, T, 0x1.5555555555555p-2);              //  1/3
+    const double* C = cold_consts() + COLD_LOG;
+    double T = C[0];
+    T = fma(x, T, C[1]);
+    T = fma(x, T, C[2]);
+    T = fma(x, T, C[3]);
+    T = fma(x, T, C[4]);
+    T = fma(x, T, C[5]);
+    T = fma(x, T, C[6]);
+    T = fma(x, T, C[7]);
     const double p = x * x;
     const double pe = fma(x, x, -p);
     const double h = -0.5 * p;                        // exact
@@ -394,11 +415,12 @@ struct ExpRed {
 };
 
 PT_CR_HD ExpRed exp_reduce(double x) {
-    const double Kd = rint(x * PT_CR_INV_LN2_128);
+    const double* C = cold_consts() + COLD_LN2_128;
+    const double Kd = rint(x * C[COLD_INV - COLD_LN2_128]);
     const int K = (int)Kd;
-    const double r0 = x - Kd * PT_CR_LN2_128_1;   // exact
-    dd m = two_prod(Kd, PT_CR_LN2_128_2);
-    m.l = fma(Kd, PT_CR_LN2_128_3, m.l);
+    const double r0 = x - Kd * C[0];   // exact
+    dd m = two_prod(Kd, C[1]);
+    m.l = fma(Kd, C[2], m.l);
     const dd h = two_sum(r0, -m.h);
     const dd r = fast_two_sum(h.h, h.l - m.l);
     return {K >> 7, K & 127, r};
@@ -412,12 +434,13 @@ PT_CR_HD ExpRed exp_reduce(double x) {
 // 2^-19.6 |r| and are evaluated in double.
 PT_CR_HD dd expm1_series_quick(dd r) {
     const double x = r.h;
-    double U = 0x1.a01a01a01a01ap-16;              // 1/8!
-    U = fma(x, U, 0x1.a01a01a01a01ap-13);          // 1/7!
-    U = fma(x, U, 0x1.6c16c16c16c17p-10);          // 1/6!
-    U = fma(x, U, 0x1.1111111111111p-7);           // 1/5!
-    U = fma(x, U, 0x1.5555555555555p-5);           // 1/4!
-    U = fma(x, U, 0x1.5555555555555p-3);           // 1/3!
+    const double* C = cold_consts() + COLD_EXP;
+    double U = C[0];
+    U = fma(x, U, C[1]);
+    U = fma(x, U, C[2]);
+    U = fma(x, U, C[3]);
+    U = fma(x, U, C[4]);
+    U = fma(x, U, C[5]);
     const double p = x * x;
     const double pe = fma(x, x, -p);
     const double h = 0.5 * p;                      // exact
@@ -486,6 +509,148 @@ PT_CR_HD double expm1_cr(double x, unsigned* ambiguous) {
     const dd q = expm1_combine<true>(R, expm1_series_quick(R.r), s);
     if (round_test(q, kEpsQuick, &out)) return out * back;
     return expm1_accurate<M>(x, ambiguous);
+}
+
+// ----------------------------------------------------------------------------------- lean phase
+//
+// What the tracking kernels evaluate at every step.  The result is held as an unnormalised pair
+// h + l with an absolute error bound e that shrinks with the square of the reduced argument, so
+// the sums need no double-double arithmetic: everything beyond the reduced argument's own high
+// part r is below 2^-16 |r| and is summed in double.  Every bound below counts the roundings of
+// those sums, each at most 2^-53 of a term no larger than 0.52 p, p = r^2.  About one argument in
+// 10^4 is left undecided and goes to the quick phase.  Straight-line code without branches: a
+// caller can interleave several evaluations.
+
+// a / b, correctly rounded, for |a|, |b| and the quotient well inside the normal range (each
+// below sits between 2^-300 and 2^300): the reciprocal refined twice and one residual correction.
+// These are the operations of the compiler's own division without its scaling and fix-up steps,
+// which act only outside that range.
+PT_CR_HD double recip_lean(double b) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    double r = __builtin_amdgcn_rcp(b);
+    r = fma(r, fma(-b, r, 1.0), r);
+    return fma(r, fma(-b, r, 1.0), r);
+#else
+    return 1.0 / b;
+#endif
+}
+// a / b from r = recip_lean(b).
+PT_CR_HD double div_by(double a, double b, double r) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    const double q = a * r;
+    return fma(fma(-b, q, a), r, q);
+#else
+    (void)r;
+    return a / b;
+#endif
+}
+PT_CR_HD double div_lean(double a, double b) { return div_by(a, b, recip_lean(b)); }
+
+// The pair h + l and its error bound e 2^-70; out = RN(h + l) is the correctly rounded value when
+// decided() says so.
+struct Lean {
+    double h, l, e;
+};
+PT_CR_HD bool decided(Lean v, double* out) {
+    const double a = v.h + fma(v.e, -0x1p-70, v.l), b = v.h + fma(v.e, 0x1p-70, v.l);
+    *out = a;
+    return a == b;
+}
+
+PT_CR_HD uint64_t bits_of(double v) {
+    uint64_t b;
+    __builtin_memcpy(&b, &v, sizeof b);
+    return b;
+}
+PT_CR_HD double of_bits(uint64_t b) {
+    double v;
+    __builtin_memcpy(&v, &b, sizeof v);
+    return v;
+}
+
+// log(yh + yl), yh in [2^-1000, 2^1000], |yl| <= ulp(yh)/2.
+//   y = 2^k m, m in [0x1.6ap-1, 0x1.6ap0), the cell's c = RN(1/centre): r = m c - 1 exactly as a
+//   pair, |r| <= 2^-8 (2^-9 where c != 1); log y = (k LN2 + Lh) + r + (r^2 V(r) + r_l + k LN2L + Ll).
+//   k LN2_42 + Lh is exact (multiples of 2^-42 below 2^10) and is 0 or at least 2^-8 > |r|, so
+//   adding r to it is an exact ordered sum.
+// Error, in units of 2^-53 p: the roundings of p, V, the three sums and the test 0.5 each, the
+// cross term r r_l that is left out 1.1, V's interpolation 2^-57.8: below 4.2; 6 is used.  k LN2L + Ll
+// and the sums with it: below 2^-94, covered by 2^-70 |A| (A = k LN2 + Lh is 0, and they with it, or
+// at least 2^-8).  Near A = 0 nothing but p counts: in nearly uniform flow the gradients have few
+// significant bits and x^2/2 falls within 10^-8 ulp of rounding midpoints.
+PT_CR_HD Lean log_lean(double yh, double yl) {
+    const uint64_t yb = bits_of(yh);
+    const uint32_t yt = (uint32_t)(yb >> 32);
+    const uint32_t t = yt - (uint32_t)PT_CR_LEAN_OFF;
+    const int32_t k = (int32_t)t >> 20;
+    const int i = (int)((t >> 12) & 255u);
+    const double m = of_bits(((uint64_t)(yt - (t & 0xfff00000u)) << 32) | (uint32_t)yb);
+    const double ml = ldexp(yl, -k);
+#if defined(__HIP_DEVICE_COMPILE__)
+    const double c = lds_lean_c[i];
+    const double2 L = lds_lean_l[i];
+    const double Lh = L.x, Ll = L.y;
+#else
+    const double c = PT_CR_LEAN_LOG[i][0], Lh = PT_CR_LEAN_LOG[i][1], Ll = PT_CR_LEAN_LOG[i][2];
+#endif
+    const double p0 = m * c;
+    const double r0 = p0 - 1.0;                                   // exact
+    const double t0 = fma(ml, c, fma(m, c, -p0));
+    const double r = r0 + t0;
+    const double rl = t0 - (r - r0);
+    const double p = r * r;
+    double V = fma(r, PT_CR_LOG_V5, PT_CR_LOG_V4);
+    V = fma(r, V, PT_CR_LOG_V3);
+    V = fma(r, V, PT_CR_LOG_V2);
+    V = fma(r, V, PT_CR_LOG_V1);
+    V = fma(r, V, PT_CR_LOG_V0);
+    const double kd = (double)k;
+    const double A = fma(kd, PT_CR_LN2_42, Lh);                   // exact
+    const double s = fma(p, V, rl) + fma(kd, PT_CR_LN2_42L, Ll);
+    const double h = A + r;
+    const double l = (r - (h - A)) + s;
+    return {h, l, fma(p, 6.0 * 0x1p17, fabs(A))};
+}
+
+// expm1(y), |y| <= 36.
+//   y = K ln2/128 + r, K = 128 k + j, r = r + r_l with |r| <= ln2/256 (the first part of ln2/128 has
+//   33 bits: y - K C1 is exact); T = 2^k 2^(j/128) as a double-double:
+//   expm1 y = (T - 1) + T r + T (r^2 V(r) + r_l) + T_l (1 + r).
+//   T - 1 is exact from T = 1/2 on, and below the ordered sum's residual makes it so; it is 0 or
+//   larger than T r, whose product is exact as a pair.
+// Error, in units of 2^-53 T p: the roundings of p, V and the four sums 0.5 each, the cross term
+// r r_l that is left out 1: below 4.3; 5 is used.  The rest (K C3 and the reduction's residual
+// below 2^-80 T, the table 2^-106 T, the sums' 2^-105) is covered by 2^-70 |T - 1|, which is 0, and
+// they with it, when K = 0 and at least 2^-8 max(T, 1) otherwise.
+PT_CR_HD Lean expm1_lean(double y) {
+    const double tk = fma(y, PT_CR_INV_LN2_128, 0x1.8p52);       // K in the low bits
+    const double Kd = tk - 0x1.8p52;
+    const int32_t K = (int32_t)(uint32_t)bits_of(tk);
+    const double r0 = fma(-Kd, PT_CR_LN2_128_1, y);
+    const double r = fma(-Kd, PT_CR_LN2_128_2, r0);
+    const double rl = fma(-Kd, PT_CR_LN2_128_2, r0 - r);
+    const int k = K >> 7;
+    const int j = K & 127;
+#if defined(__HIP_DEVICE_COMPILE__)
+    const double2 tj = lds_exp_t[j];
+    const double T = ldexp(tj.x, k), Tl = ldexp(tj.y, k);
+#else
+    const double T = ldexp(PT_CR_EXP_T[j][0], k), Tl = ldexp(PT_CR_EXP_T[j][1], k);
+#endif
+    const double p = r * r;
+    double V = fma(r, PT_CR_EXP_V4, PT_CR_EXP_V3);
+    V = fma(r, V, PT_CR_EXP_V2);
+    V = fma(r, V, PT_CR_EXP_V1);
+    V = fma(r, V, PT_CR_EXP_V0);
+    const double s = fma(p, V, rl);
+    const double A = T - 1.0;
+    const double Al = T - (A + 1.0);
+    const double P = T * r;
+    const double Pl = fma(T, r, -P);
+    const double u = fma(T, s, (fma(Tl, r, Pl) + Tl) + Al);
+    const double h = A + P;
+    const double l = (P - (h - A)) + u;
+    return {h, l, fma(T * p, 5.0 * 0x1p17, fabs(A))};
 }
 
 }  // namespace ptcr

@@ -32,3 +32,18 @@ extern "C" void ptcr_phases(int fn, const double* x, double* qh, double* ql, dou
         qh[i] = q.h; ql[i] = q.l; ah[i] = a.h; al[i] = a.l;
     }
 }
+
+// The lean phase: its pair and error bound, and its rounded value with the verdict (1 decided).
+extern "C" void ptcr_lean(int fn, const double* x, double* h, double* l, double* e, double* y, int* ok, long n) {
+    for (long i = 0; i < n; ++i) {
+        ptcr::Lean v;
+        if (fn == 1) {
+            v = ptcr::expm1_lean(x[i]);
+        } else {
+            const ptcr::dd a = fn == 0 ? ptcr::two_sum(1.0, x[i]) : ptcr::dd{x[i], 0.0};
+            v = ptcr::log_lean(a.h, a.l);
+        }
+        h[i] = v.h; l[i] = v.l; e[i] = v.e;
+        ok[i] = ptcr::decided(v, &y[i]) ? 1 : 0;
+    }
+}

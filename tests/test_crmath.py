@@ -155,3 +155,41 @@ def test_small_arguments_near_midpoints(libs, fn):
                     close += 1
     assert np.array_equal(y, want), (fn, x[y != want][:5])
     assert amb <= close, (fn, amb, close)
+
+
+def _lean_inputs(fn, rng, n):
+    """The lean phase's range: ordinary gradients, near-uniform flow (arguments down to 2^-60), and
+    the edges of its table cells and of its reduction steps."""
+    near = rng.choice([-1.0, 1.0], n) * np.exp(rng.uniform(np.log(2.0 ** -60), np.log(0.02), n))
+    if fn == "expm1":
+        k = np.arange(-6600, 6600) + 0.5
+        edges = np.concatenate([k * np.log(2) / 128 * (1 + d) for d in (-2.0 ** -50, 0.0, 2.0 ** -50)])
+        return np.concatenate([rng.uniform(-36, 36, n), rng.uniform(-1.5, 1.5, n), near, edges[np.abs(edges) <= 36], [36.0, -36.0]])
+    cells = (np.arange(0x3FE6A000, 0x3FF6B000, 0x1000, dtype=np.int64) << 32).view(np.float64)
+    edges = np.concatenate([cells, np.nextafter(cells, 0), np.nextafter(cells, 2)])
+    if fn == "log":
+        return np.concatenate([np.exp(rng.uniform(-600, 600, n)), rng.uniform(1e-6, 2.0, n), edges, edges * 2.0 ** -30])
+    x = np.concatenate([rng.uniform(-0.5, 0.5, n), np.exp(rng.uniform(-1, 80, n)), near, edges - 1.0])
+    return x[(x >= -0.5) & (x != 0.0)]
+
+
+@pytest.mark.parametrize("fn", sorted(FN))
+def test_lean_phase(libs, fn):
+    """The lean pair h + l lies within its own error bound of the exact value, what it decides is the
+    correctly rounded value, and it leaves few ordinary arguments to the quick phase."""
+    S, Q = libs
+    S.ptcr_lean.argtypes = [ctypes.c_int] + [ctypes.c_void_p] * 6 + [ctypes.c_long]
+    rng = np.random.Generator(np.random.PCG64(FN[fn] + 400))
+    x = np.ascontiguousarray(_lean_inputs(fn, rng, 200_000))
+    h, l, e, y, r, m = (np.empty_like(x) for _ in range(6))
+    ok = np.empty(x.size, np.int32)
+    S.ptcr_lean(FN[fn], x.ctypes.data, h.ctypes.data, l.ctypes.data, e.ctypes.data, y.ctypes.data, ok.ctypes.data, x.size)
+    Q.quad_relerr(FN[fn], x.ctypes.data, h.ctypes.data, l.ctypes.data, m.ctypes.data, x.size)
+    Q.quad_eval(FN[fn], x.ctypes.data, r.ctypes.data, None, x.size)
+    e *= 2.0 ** -70
+    bad = m * np.abs(r) > e
+    assert not bad.any(), (x[bad][:5], (m * np.abs(r) / e)[bad][:5])
+    d = ok == 1
+    assert np.array_equal(y[d], r[d]), (x[d][y[d] != r[d]][:5])
+    ordinary = (np.abs(x) > 0.05) if fn != "log" else (np.abs(np.log(x)) > 0.05)
+    assert np.mean(~d[ordinary]) < 2.0 ** -11
