@@ -474,28 +474,6 @@ int make_plan(const pt_grid* const* grids, int32_t n_grids, const pt_particles* 
     P.key.layout = quad ? L_QUAD : (o->layout == PT_LAYOUT_FACES ? L_FACES : L_CELL);
     P.key.out = P.ts ? O_SERIES : (P.path ? O_PATH : O_END);
     P.key.batched = P.multi ? 1 : 0;
-    P.key.sched = o->schedule == PT_SCHED_STATIC ? S_STATIC : S_PERSISTENT;
-    P.fn = track_kernel(P.key);
-    P.block = o->block ? o->block : 256;
-    if (P.key.sched == S_STATIC) {
-        // a multiple of 8 chunks of blocks: chunks are dealt to the dies round robin
-        const int64_t nb = std::max<int64_t>(1, (p->n + P.block - 1) / P.block);
-        const int64_t m = (int64_t)kXcd * kDieChunk;
-        P.grid = (int)((nb + m - 1) / m * m);
-    } else {
-        int per_cu = o->blocks_per_cu;
-        if (!per_cu) {
-            int occ = 0;
-            if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, P.fn, P.block, 0) != hipSuccess || occ < 1) {
-                (void)hipGetLastError();
-                occ = 2;
-            }
-            per_cu = occ;
-        }
-        P.grid = std::max(1, n_cu * per_cu);
-        const int64_t need = (p->n + P.block - 1) / P.block;
-        if (need < P.grid) P.grid = (int)std::max<int64_t>(1, need);
-    }
     P.b_grids = P.multi ? align_up(sizeof(GridDev) * n_grids, 256) : 0;
     P.b_offs = P.batched ? align_up(sizeof(int64_t) * (P.n_groups + 1), 256) : 0;
     P.b_gg = P.batched ? align_up(sizeof(int32_t) * P.n_groups, 256) : 0;
@@ -525,6 +503,46 @@ int make_plan(const pt_grid* const* grids, int32_t n_grids, const pt_particles* 
             return fail(PT_ERR_UNSUPPORTED, "ordering %lld particles needs %zu bytes of buffer, above the %zu available",
                         (long long)p->n, P.sort_bytes, sort_budget);
         if (!P.sort) P.sort_bytes = 0;
+    }
+    // PT_SCHED_AUTO.  The static kernel runs ordered work (the lanes of a wave finish close together)
+    // and work that the chip holds at once, up to twice over; the persistent kernel's refills pay
+    // only for more particles than that in index order, when their path lengths differ much (its
+    // loop costs ~900 cycles a step more and holds 3 waves per SIMD).  Call times, static against
+    // persistent: 1e6 in order 1.97 / 2.63 ms, 4e6 with wells in order 11.2 / 12.9 ms, unordered
+    // 18.0 / 13.3 ms; 10,000 on 2,200-step paths 2.59 / 3.34 ms; 300,000 on a quadtree unordered
+    // 0.88 / 1.00 ms.
+    const int64_t resident = (int64_t)n_cu * 4 * 64 * waves_static(P.key.precision, P.key.out);
+    if (o->schedule == PT_SCHED_AUTO) P.key.sched = (P.sort || p->n <= 2 * resident) ? S_STATIC : S_PERSISTENT;
+    else P.key.sched = o->schedule == PT_SCHED_STATIC ? S_STATIC : S_PERSISTENT;
+    P.fn = track_kernel(P.key);
+    P.block = o->block;
+    if (P.key.sched == S_STATIC) {
+        // Default block.  One wave when the particles give each compute unit at most one (a block
+        // of four would leave compute units idle: 4,096 particles 275 / 286 us), and when each
+        // lane's place is taken eight times or more (no wave waits for its block's slowest: 4e6 with
+        // wells 11.2 / 12.9 ms).  In between four waves, which spread evenly over a compute unit's
+        // SIMDs when the last blocks drain (1e6: 1.97 / 2.14 ms; transient 5e5: 1.47 / 1.57 ms); always
+        // four where every thread holds LDS slots (snapshots, 2e5: 2.14 / 2.85 ms).
+        const bool slots = P.key.out != O_END;
+        if (!P.block) P.block = (p->n <= (int64_t)64 * n_cu || (p->n >= 8 * resident && !slots)) ? 64 : 256;
+        // a multiple of 8 chunks of blocks: chunks are dealt to the dies round robin
+        const int64_t nb = std::max<int64_t>(1, (p->n + P.block - 1) / P.block);
+        const int64_t m = (int64_t)kXcd * kDieChunk;
+        P.grid = (int)((nb + m - 1) / m * m);
+    } else {
+        if (!P.block) P.block = 256;
+        int per_cu = o->blocks_per_cu;
+        if (!per_cu) {
+            int occ = 0;
+            if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, P.fn, P.block, 0) != hipSuccess || occ < 1) {
+                (void)hipGetLastError();
+                occ = 2;
+            }
+            per_cu = occ;
+        }
+        P.grid = std::max(1, n_cu * per_cu);
+        const int64_t need = (p->n + P.block - 1) / P.block;
+        if (need < P.grid) P.grid = (int)std::max<int64_t>(1, need);
     }
     P.b_base = (P.sort && P.batched) ? align_up(sizeof(int64_t) * n_grids, 256) : 0;
     P.tables = P.b_grids + P.b_offs + P.b_gg + P.b_snap + P.b_tstep + P.b_base;

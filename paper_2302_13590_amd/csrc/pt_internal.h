@@ -215,6 +215,10 @@ enum Precision { P64 = 0, PMIX = 1 };
 enum Layout { L_FACES = 1, L_CELL = 2, L_QUAD = 3 };
 enum Sched { S_STATIC = 1, S_PERSISTENT = 2 };
 
+// Waves per SIMD the static kernels are built for (lanes resident on a compute unit: 4 SIMDs x
+// waves x 64); the reasons and the persistent kernels' counts are with the kernels.
+constexpr int waves_static(int prec, int out) { return prec == P64 ? 4 : (out == 0 ? 8 : 6); }
+
 struct KernelKey {
     int precision, layout, out, batched, sched;   // out: O_END / O_SERIES / O_PATH
 };

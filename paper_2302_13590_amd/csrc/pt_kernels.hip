@@ -1317,7 +1317,7 @@ __device__ __forceinline__ void finish_fast(Lane<PREC>& L, int32_t st, const Tra
 constexpr int kFastCr = ptcr::CR_FLAG;
 
 template <int PREC, int OUT>
-constexpr int kWavesStatic = PREC == P64 ? 4 : (OUT == O_END ? 8 : 6);
+constexpr int kWavesStatic = waves_static(PREC, OUT);
 // Persistent kernel: FP64 three (168 VGPRs instead of ~175, a few bytes of rarely used values in
 // scratch: C3 -20%, C2 -13%; four spill 110-230 bytes per lane and are slower); mixed six for
 // endpoint runs (C4 -7%), four otherwise.
@@ -1327,19 +1327,20 @@ constexpr int kWavesPersistent = PREC == P64 ? 3 : (OUT == O_END ? 6 : 4);
 template <int PREC, int LAYOUT, int OUT, bool BATCHED>
 __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kWavesStatic<PREC, OUT>)))
 k_track_static(TrackParams P) {
-    __shared__ BlockShared<OUT == O_SERIES> S;
-    const double* snap = block_setup<PREC, OUT == O_SERIES>(S, P);
-    unsigned long long crossings = 0;
-    Lane<PREC> L;
-    L.amb = 0u;
-    L.drop = 0u;
     // Block b runs on die b mod 8.  The slots are dealt to the dies in chunks of kDieChunk
     // consecutive blocks, round robin: a die's concurrent blocks hold neighbouring particles
     // (they share record lines in its L2), and every die sweeps the whole ordered work, so no die
     // is left with a heavier part of it (gridDim.x is a multiple of 8 * kDieChunk).
     const int64_t die = blockIdx.x % kXcd, j = blockIdx.x / kXcd;
     const int64_t blk = ((j / kDieChunk) * kXcd + die) * kDieChunk + j % kDieChunk;
+    if (blk * blockDim.x >= P.n) return;   // the whole block is padding
     const int64_t slot = blk * blockDim.x + threadIdx.x;
+    __shared__ BlockShared<OUT == O_SERIES> S;
+    const double* snap = block_setup<PREC, OUT == O_SERIES>(S, P);
+    unsigned long long crossings = 0;
+    Lane<PREC> L;
+    L.amb = 0u;
+    L.drop = 0u;
     if constexpr (OUT == O_SERIES && kPacked<LAYOUT>) {
         // timeseries: the wave steps its lanes together so that it can evaluate the deferred
         // snapshots of all of them at once
