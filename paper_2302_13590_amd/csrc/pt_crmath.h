@@ -87,13 +87,13 @@ PT_CR_TABLE double PT_CR_COLD_C[21] = {
     PT_CR_LN2_H, PT_CR_LN2_L, PT_CR_LN2_128_1, PT_CR_LN2_128_2, PT_CR_LN2_128_3, PT_CR_INV_LN2_128, PT_CR_SQRT2};
 enum { COLD_LOG = 0, COLD_EXP = 8, COLD_LN2 = 14, COLD_LN2_128 = 16, COLD_INV = 19, COLD_SQRT2 = 20 };
 
-PT_CR_HD const double* cold_consts() {
-    const double* c = PT_CR_COLD_C;
+PT_CR_HD const double* opaque(const double* c) {   // loaded here, not hoisted
 #if defined(__HIP_DEVICE_COMPILE__) && defined(__OPTIMIZE__)
-    asm volatile("" : "+s"(c));   // opaque: loaded here, not hoisted
+    asm volatile("" : "+s"(c));
 #endif
     return c;
 }
+PT_CR_HD const double* cold_consts() { return opaque(PT_CR_COLD_C); }
 
 PT_CR_HD dd two_sum(double a, double b) {
     const double s = a + b;
@@ -324,11 +324,12 @@ PT_CR_HD dd log1p_series_quick(dd r) {
 // log1p(r) for |r| < 2^-8.4 with relative error < 2^-100.
 PT_CR_HD dd log1p_series_accurate(dd r) {
     // log1p(r) = r * sum_{k>=1} (-1)^(k+1) r^(k-1) / k, Horner from k = 14
-    dd S = {PT_CR_INVK[14][0], PT_CR_INVK[14][1]};
+    const double* C = opaque(PT_CR_INVK[0]);
+    dd S = {C[28], C[29]};
     S.h = -S.h;
     S.l = -S.l;
     for (int k = 13; k >= 1; --k) {
-        dd c = {PT_CR_INVK[k][0], PT_CR_INVK[k][1]};
+        dd c = {C[2 * k], C[2 * k + 1]};
         if (!(k & 1)) {
             c.h = -c.h;
             c.l = -c.l;
@@ -451,8 +452,9 @@ PT_CR_HD dd expm1_series_quick(dd r) {
 
 // e^r - 1 for |r| <= ln2/256 with relative error < 2^-100.
 PT_CR_HD dd expm1_series_accurate(dd r) {
-    dd S = {PT_CR_INVF[15][0], PT_CR_INVF[15][1]};
-    for (int k = 14; k >= 1; --k) S = dd_add({PT_CR_INVF[k][0], PT_CR_INVF[k][1]}, dd_mul(r, S));
+    const double* C = opaque(PT_CR_INVF[0]);
+    dd S = {C[30], C[31]};
+    for (int k = 14; k >= 1; --k) S = dd_add({C[2 * k], C[2 * k + 1]}, dd_mul(r, S));
     return dd_mul(r, S);
 }
 
@@ -520,6 +522,19 @@ PT_CR_HD double expm1_cr(double x, unsigned* ambiguous) {
 // those sums, each at most 2^-53 of a term no larger than 0.52 p, p = r^2.  About one argument in
 // 10^4 is left undecided and goes to the quick phase.  Straight-line code without branches: a
 // caller can interleave several evaluations.
+
+// a b + c with a constant c.  On the device c stays in scalar registers (the compiler would copy
+// each constant of a polynomial into a vector pair for the two-operand form: a move and two
+// registers a step).
+PT_CR_HD double fma_c(double a, double b, double c) {
+#if defined(__HIP_DEVICE_COMPILE__) && defined(__OPTIMIZE__)
+    double d;
+    asm("v_fma_f64 %0, %1, %2, %3" : "=v"(d) : "v"(a), "v"(b), "s"(c));
+    return d;
+#else
+    return fma(a, b, c);
+#endif
+}
 
 // a / b, correctly rounded, for |a|, |b| and the quotient well inside the normal range (each
 // below sits between 2^-300 and 2^300): the reciprocal refined twice and one residual correction.
@@ -600,9 +615,9 @@ PT_CR_HD Lean log_lean(double yh, double yl) {
     const double rl = t0 - (r - r0);
     const double p = r * r;
     double V = fma(r, PT_CR_LOG_V5, PT_CR_LOG_V4);
-    V = fma(r, V, PT_CR_LOG_V3);
-    V = fma(r, V, PT_CR_LOG_V2);
-    V = fma(r, V, PT_CR_LOG_V1);
+    V = fma_c(r, V, PT_CR_LOG_V3);
+    V = fma_c(r, V, PT_CR_LOG_V2);
+    V = fma_c(r, V, PT_CR_LOG_V1);
     V = fma(r, V, PT_CR_LOG_V0);
     const double kd = (double)k;
     const double A = fma(kd, PT_CR_LN2_42, Lh);                   // exact
@@ -639,8 +654,8 @@ PT_CR_HD Lean expm1_lean(double y) {
 #endif
     const double p = r * r;
     double V = fma(r, PT_CR_EXP_V4, PT_CR_EXP_V3);
-    V = fma(r, V, PT_CR_EXP_V2);
-    V = fma(r, V, PT_CR_EXP_V1);
+    V = fma_c(r, V, PT_CR_EXP_V2);
+    V = fma_c(r, V, PT_CR_EXP_V1);
     V = fma(r, V, PT_CR_EXP_V0);
     const double s = fma(p, V, rl);
     const double A = T - 1.0;
