@@ -443,10 +443,9 @@ struct Plan {
     // per-call tables (256-byte aligned segments): grid views, group table, snapshot times, time
     // step ends, first global cell of each grid (batched ordering)
     size_t b_grids = 0, b_offs = 0, b_gg = 0, b_snap = 0, b_tstep = 0, b_base = 0, tables = 0;
-    // ordering by starting cell: order, bucket, super-bucket-ordered buckets and indices [n] each,
-    // the tiles' super-bucket counts, scan tile sums
-    int32_t shift = 0, nbuckets = 0, fine = 0, nsuper = 0, ptiles = 0, ntiles = 0;
-    int64_t ncnt = 0;
+    // ordering by starting cell: bucket (then the order), super-bucket-ordered buckets and indices
+    // [n] each, the tiles' starts in the super-buckets, the super-buckets' totals
+    int32_t shift = 0, nbuckets = 0, fine = 0, nsuper = 0, ptiles = 0, tile = 0;
     size_t b_order = 0, b_cnt = 0, sort_bytes = 0;
     // pathline count pass: tile sums of the offset scan
     int64_t scan_ntiles = 0;
@@ -492,16 +491,20 @@ int make_plan(const pt_grid* const* grids, int32_t n_grids, const pt_particles* 
         // most kFineMax buckets
         P.fine = (int32_t)std::min<int64_t>(kFineMax, std::max<int64_t>(1, (P.nbuckets + 511) / 512));
         P.nsuper = (P.nbuckets + P.fine - 1) / P.fine;
-        P.ptiles = (int32_t)((p->n + kSortTile - 1) / kSortTile);
-        P.ncnt = (int64_t)P.nsuper * P.ptiles;
-        P.ntiles = (int32_t)((P.ncnt + kScanTile - 1) / kScanTile);
+        P.tile = p->n < kSortSmall ? 1024 : (p->n < kSortBig ? kSortTile : kSortTileMax);
+        P.ptiles = (int32_t)((p->n + P.tile - 1) / P.tile);
         P.b_order = align_up(sizeof(int32_t) * (size_t)p->n, 256);
-        P.b_cnt = align_up(sizeof(unsigned) * (size_t)P.ncnt, 256);
-        P.sort_bytes = 4 * P.b_order + P.b_cnt + sizeof(unsigned) * (size_t)P.ntiles;
-        P.sort = P.sort_bytes <= sort_budget;
+        P.b_cnt = align_up(sizeof(unsigned) * (size_t)P.nsuper * (size_t)P.ptiles, 256);
+        P.sort_bytes = 3 * P.b_order + P.b_cnt + sizeof(unsigned) * (size_t)P.nsuper;
+        // what may be ordered is a documented size: 16 bytes per particle and 4 per super-bucket and
+        // tile of 4096 (above the bytes used, which a small call's totals do not make large)
+        const size_t tiles = (size_t)((p->n + kSortTile - 1) / kSortTile) * (size_t)P.nsuper;
+        const size_t stated = 4 * P.b_order + align_up(sizeof(unsigned) * tiles, 256) +
+                              sizeof(unsigned) * ((tiles + (size_t)kScanTile - 1) / (size_t)kScanTile);
+        P.sort = std::max(stated, P.sort_bytes) <= sort_budget;
         if (!P.sort && o->sort == PT_SORT_CELL)
             return fail(PT_ERR_UNSUPPORTED, "ordering %lld particles needs %zu bytes of buffer, above the %zu available",
-                        (long long)p->n, P.sort_bytes, sort_budget);
+                        (long long)p->n, stated, sort_budget);
         if (!P.sort) P.sort_bytes = 0;
     }
     // PT_SCHED_AUTO.  The static kernel runs ordered work (the lanes of a wave finish close together)
@@ -674,8 +677,7 @@ void bind_params(const Plan& PL, const pt_grid* const* grids, int32_t n_grids, c
         SP.fine = PL.fine;
         SP.nsuper = PL.nsuper;
         SP.ptiles = PL.ptiles;
-        SP.ncnt = PL.ncnt;
-        SP.ntiles = PL.ntiles;
+        SP.tile = PL.tile;
         SP.n = p->n;
         SP.cell = p->cell;
         SP.status = p->status;
@@ -684,11 +686,11 @@ void bind_params(const Plan& PL, const pt_grid* const* grids, int32_t n_grids, c
         SP.group_grid = P.group_grid;
         SP.grid_base = PL.batched ? reinterpret_cast<const int64_t*>(d_tables + (PL.tables - PL.b_base)) : nullptr;
         SP.order = reinterpret_cast<int32_t*>(d_sort);
-        SP.bucket = reinterpret_cast<unsigned*>(d_sort + PL.b_order);
-        SP.sbucket = reinterpret_cast<unsigned*>(d_sort + 2 * PL.b_order);
-        SP.sidx = reinterpret_cast<int32_t*>(d_sort + 3 * PL.b_order);
-        SP.cnt = reinterpret_cast<unsigned*>(d_sort + 4 * PL.b_order);
-        SP.part = reinterpret_cast<unsigned*>(d_sort + 4 * PL.b_order + PL.b_cnt);
+        SP.bucket = reinterpret_cast<unsigned*>(d_sort);
+        SP.sbucket = reinterpret_cast<unsigned*>(d_sort + PL.b_order);
+        SP.sidx = reinterpret_cast<int32_t*>(d_sort + 2 * PL.b_order);
+        SP.cnt = reinterpret_cast<unsigned*>(d_sort + 3 * PL.b_order);
+        SP.total = reinterpret_cast<unsigned*>(d_sort + 3 * PL.b_order + PL.b_cnt);
         P.order = SP.order;
     }
 }
@@ -709,20 +711,25 @@ struct LaunchSeq {
     }
 };
 
+ResetParams reset_params(Counters* c, const SortParams& SP) {
+    ResetParams R;
+    std::memset(&R, 0, sizeof R);
+    R.c = c;
+    R.total = SP.total;
+    R.nsuper = SP.nsuper;
+    return R;
+}
+
 // Counter reset, ordering sort, tracking kernel, pathline offset scan.  The argument blocks
 // are referenced, not copied: they must outlive the launches (or graph construction).
-void build_seq(const Plan& PL, int64_t n, Counters** cptr, TrackParams* P, SortParams* SP, ScanParams* SC,
+void build_seq(const Plan& PL, int64_t n, ResetParams* RP, TrackParams* P, SortParams* SP, ScanParams* SC,
                LaunchSeq& seq) {
-    seq.push(reset_kernel(), dim3(1), dim3(64), cptr, sizeof *cptr);
+    seq.push(reset_kernel(), dim3(1), dim3(256), RP, sizeof *RP);
     if (n > 0) {
         if (PL.sort) {
-            const unsigned nt = (unsigned)SP->ptiles;
-            seq.push(sort_tiles_kernel(), dim3(nt), dim3(256), SP, sizeof *SP);
-            seq.push(sort_scan_tiles_kernel(), dim3((unsigned)SP->ntiles), dim3(kScanBlock), SP, sizeof *SP);
-            seq.push(sort_scan_partials_kernel(), dim3(1), dim3(kScanBlock), SP, sizeof *SP);
-            if (SP->ntiles > 1)
-                seq.push(sort_scan_add_kernel(), dim3((unsigned)SP->ntiles), dim3(kScanBlock), SP, sizeof *SP);
-            seq.push(sort_spread_kernel(), dim3(nt), dim3(256), SP, sizeof *SP);
+            const unsigned nt = (unsigned)SP->ptiles, threads = (unsigned)std::min(1024, SP->tile / kSortPer);
+            seq.push(sort_tiles_kernel(), dim3(nt), dim3(threads), SP, sizeof *SP);
+            seq.push(sort_spread_kernel(), dim3(nt), dim3(threads), SP, sizeof *SP);
             seq.push(sort_fine_kernel(), dim3((unsigned)SP->nsuper), dim3(kFineBlock), SP, sizeof *SP);
         }
         seq.track_at = seq.n;
@@ -1132,9 +1139,9 @@ int pt_track(const pt_grid* const* grids, int32_t n_grids, const pt_particles* p
     bind_params(PL, grids, n_grids, p, o, static_cast<unsigned char*>(r->d_tables),
                 static_cast<unsigned char*>(r->d_sort), static_cast<int64_t*>(r->d_scan),
                 static_cast<unsigned char*>(r->d_recheck), r->d_counters, P, SP, SC);
-    Counters* cptr = r->d_counters;
+    ResetParams RP = reset_params(r->d_counters, SP);
     LaunchSeq seq;
-    build_seq(PL, p->n, &cptr, &P, &SP, &SC, seq);
+    build_seq(PL, p->n, &RP, &P, &SP, &SC, seq);
 
     hipError_t e = hipEventRecord(r->ev0, s);
     if (e == hipSuccess) {
@@ -1260,7 +1267,8 @@ int pt_track_noalloc(const pt_grid* const* grids, int32_t n_grids, const pt_part
     tf.flush();
     hipError_t e = tf.err;
     LaunchSeq seq;
-    build_seq(PL, p->n, &cptr, &P, &SP, &SC, seq);
+    ResetParams RP = reset_params(cptr, SP);
+    build_seq(PL, p->n, &RP, &P, &SP, &SC, seq);
     CountsParams CP;
     CP.c = cptr;
     CP.out = counts;

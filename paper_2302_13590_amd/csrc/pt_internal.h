@@ -174,12 +174,15 @@ struct ScanParams {
 };
 
 // Spatial ordering of particles by starting cell (one bucket per cell, or per run of 2^shift
-// cells on grids of more than kMaxBuckets cells), in two levels without global returning
-// atomics: tiles of kSortTile particles count their particles per super-bucket (a run of `fine`
-// consecutive buckets) in LDS, an exclusive scan of those counts (super-bucket-major) places
-// every tile's share of every super-bucket, and one block per super-bucket then orders its range
-// by bucket with an LDS histogram.
-constexpr int kSortTile = 4096;      // particles per tile (256 threads x 16)
+// cells on grids of more than kMaxBuckets cells), in two levels: tiles of particles count their
+// particles per super-bucket (a run of `fine` consecutive buckets) in LDS and claim their share of
+// each super-bucket with one global atomic; every tile then places its particles; and one block
+// per super-bucket orders its range by bucket with an LDS histogram.
+constexpr int kSortTile = 4096;      // particles per tile up to kSortBig, 1024 below kSortSmall
+constexpr int kSortTileMax = 16384;  //   (more tiles than compute units early) and 16384 above
+constexpr int64_t kSortSmall = (int64_t)1 << 18;   // kSortBig (each tile claims from hundreds of
+constexpr int64_t kSortBig = (int64_t)1 << 23;     //   super-buckets, at ~25 G atomics/s)
+constexpr int kSortPer = 4;          // particles per thread and round, at most 1024 threads
 constexpr int kFineMax = 8192;       // buckets per super-bucket at most (a 32 KB LDS histogram)
 constexpr int kMaxSuper = 2048;      // super-buckets at most (kMaxBuckets / kFineMax)
 constexpr int kFineBlock = 1024;     // threads of the per-super-bucket pass (= kScanBlock)
@@ -196,17 +199,16 @@ struct SortParams {
     int32_t nbuckets;
     int32_t fine;                   // buckets per super-bucket
     int32_t nsuper;                 // super-buckets
-    int32_t ptiles;                 // tiles of kSortTile particles
-    int64_t ncnt;                   // nsuper * ptiles
-    int32_t ntiles;                 // tiles of kScanTile entries in the scan of cnt
+    int32_t ptiles;                 // tiles
+    int32_t tile;                   // particles per tile
     int32_t pad;
-    unsigned* cnt;                  // [nsuper][ptiles] particles of each tile in each super-bucket,
-                                    //   then their exclusive prefix sums (super-bucket-major)
-    unsigned* part;                 // [ntiles] scan tile totals, then their exclusive prefix sums
+    unsigned* total;                // [nsuper] particles of each super-bucket (cleared by the reset)
+    unsigned* cnt;                  // [ptiles][nsuper] where the tile's share of a super-bucket starts
+                                    //   inside it
     unsigned* bucket;               // [n] bucket of each particle
     unsigned* sbucket;              // [n] buckets in super-bucket order
     int32_t* sidx;                  // [n] particle indices in super-bucket order
-    int32_t* order;                 // [n]
+    int32_t* order;                 // [n], over bucket (dead once the particles are placed)
 };
 constexpr int64_t kMaxBuckets = (int64_t)1 << 24;   // one bucket per cell up to 2^24 cells
 static_assert((int64_t)kMaxSuper * kFineMax >= kMaxBuckets, "super-buckets cover every bucket");
@@ -228,9 +230,6 @@ const void* track_kernel(const KernelKey& k);
 const void* careful_kernel(const KernelKey& k);        // FP64 keys only
 const void* reset_kernel();
 const void* sort_tiles_kernel();
-const void* sort_scan_tiles_kernel();
-const void* sort_scan_partials_kernel();
-const void* sort_scan_add_kernel();
 const void* sort_spread_kernel();
 const void* sort_fine_kernel();
 const void* scan_tiles_kernel();
@@ -238,6 +237,14 @@ const void* scan_partials_kernel();
 const void* scan_add_kernel();
 const void* build_kernel();
 const void* build_quad_kernel();
+
+// Reset kernel arguments: the counters, and the super-bucket totals of an ordered call.
+struct ResetParams {
+    Counters* c;
+    unsigned* total;
+    int32_t nsuper;
+    int32_t pad;
+};
 
 // Grid build kernel arguments.
 struct BuildParams {

@@ -215,25 +215,25 @@ __device__ __forceinline__ void estimate_exit64(const double (&u1)[3], const dou
                                                 const double (&xi)[3], Exit64& X) {
     float E[3];
     double D[3], ue[3];
-    bool pos[3];
     X.sure = true;
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
         X.A[a] = u2[a] - u1[a];
         X.up[a] = u1[a] + X.A[a] * xi[a];
-        pos[a] = X.up[a] > 0.0;
-        ue[a] = pos[a] ? u2[a] : u1[a];
-        D[a] = (pos[a] ? 1.0 : 0.0) - xi[a];
-        const bool feasible = (pos[a] & (u2[a] > 0.0)) | ((X.up[a] < 0.0) & (u1[a] < 0.0));
+        const bool pos = X.up[a] > 0.0, neg = X.up[a] < 0.0;
+        const bool out2 = u2[a] > 0.0, out1 = u1[a] < 0.0;
+        ue[a] = pos ? u2[a] : u1[a];
+        D[a] = (pos ? 1.0 : 0.0) - xi[a];
+        const bool feasible = ((int)pos & (int)out2) | ((int)neg & (int)out1);
         bool sure;
         const float est = exit_estimate(D[a], X.up[a], X.A[a], ue[a], sure);
         E[a] = feasible ? est : __builtin_inff();
-        X.sure = X.sure & (sure | !feasible);
+        X.sure = (int)X.sure & ((int)sure | (int)!feasible);
     }
     const float Ew = fminf(fminf(E[0], E[1]), E[2]);
     const float second = __builtin_amdgcn_fmed3f(E[0], E[1], E[2]);
     // a second axis inside the margin, or (inf <= inf) no axis at all
-    X.sure = X.sure & !(second <= Ew * (1.0f + (float)kFilterMargin));   // 1 + 2^-15 is a float
+    X.sure = (int)X.sure & (int)!(second <= Ew * (1.0f + (float)kFilterMargin));   // 1 + 2^-15 is a float
     X.c0 = E[0] == Ew;
     X.c1 = E[1] == Ew;
     X.D = sel3(X.c0, X.c1, D[0], D[1], D[2]);
@@ -259,7 +259,7 @@ __device__ __forceinline__ double exit_time64_lean(const Exit64& X, bool& ok) {
     const double yl = ratio ? 0.0 : sml - (s - big);
     double L;
     const bool done = ptcr::decided(ptcr::log_lean(yh, yl), &L);
-    ok = ok & done;
+    ok = (int)ok & (int)done;
     const double q = ptcr::div_lean(L, ratio ? X.Aw : x);
     double dt = ratio ? q : r * q;
     dt = (fabs(x) < 0x1p-60) ? r : dt;
@@ -1525,31 +1525,39 @@ __global__ void k_counts(CountsParams C) {
     C.out[15] = 0;
 }
 
-__global__ void k_reset(Counters* c) {
-    unsigned long long* w = reinterpret_cast<unsigned long long*>(c);
+__global__ void __launch_bounds__(256) k_reset(ResetParams R) {
+    unsigned long long* w = reinterpret_cast<unsigned long long*>(R.c);
     const int n = sizeof(Counters) / sizeof(unsigned long long);
     if ((int)threadIdx.x < n) w[threadIdx.x] = 0ull;
+    for (int q = threadIdx.x; q < R.nsuper; q += blockDim.x) R.total[q] = 0u;
 }
 
 // ---------------------------------------------------------------------------------------------
-// Block-wide inclusive scan of one value per thread (Hillis-Steele in LDS).
-__device__ __forceinline__ int64_t block_scan(int64_t* part, int64_t x) {
-    part[threadIdx.x] = x;
-    __syncthreads();
-    for (int off = 1; off < kScanBlock; off <<= 1) {
-        const int64_t a = (threadIdx.x >= (unsigned)off) ? part[threadIdx.x - off] : 0;
-        __syncthreads();
-        part[threadIdx.x] += a;
-        __syncthreads();
+// Block-wide inclusive scan of one value per thread: within each wave by shuffles, then the sums
+// of the waves before it (two barriers; a scan in LDS over 1024 threads took twenty).  `part`:
+// one entry per wave.
+template <class T>
+__device__ __forceinline__ T block_scan(T* part, T x) {
+    const int lane = (int)(threadIdx.x & 63u), wave = (int)(threadIdx.x >> 6);
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+        const T v = __shfl_up(x, off, 64);
+        if (lane >= off) x += v;
     }
-    return part[threadIdx.x];
+    __syncthreads();   // `part` may still be read from an earlier scan
+    if (lane == 63) part[wave] = x;
+    __syncthreads();
+    for (int q = 0; q < wave; ++q) x += part[q];
+    return x;
 }
 
-// Spatial ordering: the particles sorted by their starting cell (bucket), in two levels with LDS
-// counters only -- returning atomics on a global histogram run at the L2 atomic units' ~25 G/s
-// on random buckets, which made a one-level counting sort of 1.8e7 particles take 1 ms.  Ranks
-// inside a bucket come from LDS atomics, so the order inside a bucket is arbitrary.  The order
-// only changes which lanes and dies process which particles, never a result.
+// Spatial ordering: the particles sorted by their starting cell (bucket), in two levels.  A
+// returning global atomic for every particle runs at the L2 atomic units' ~25 G/s on random
+// buckets, which made a one-level counting sort of 1.8e7 particles take 1 ms; here a tile makes one
+// per super-bucket it holds.  Bound by launches and by the latency of each kernel's few loads up to
+// ~1e6 particles: three kernels instead of six with a scan of the tile counts, 1e5 particles
+// 57 -> 30 us, 1e6 67 -> 45 us, 1.8e7 462 -> 376 us.  The order inside a bucket is arbitrary: it only
+// changes which lanes and dies process which particles, never a result.
 
 // The group of particle p: the last group whose first particle is at or before p, searched in
 // [lo, n_groups).
@@ -1584,14 +1592,14 @@ __device__ __forceinline__ uint32_t sort_bucket(const SortParams& S, int64_t p) 
     return (uint32_t)(b < S.nbuckets ? b : S.nbuckets - 1);
 }
 
-// Level 1: each tile of kSortTile particles keeps its particles' buckets and counts them per
-// super-bucket; the counts go to cnt[super][tile].
-__global__ void __launch_bounds__(256) k_sort_tiles(SortParams S) {
+// Level 1: each tile keeps its particles' buckets, counts them per super-bucket, and claims a
+// range of each super-bucket.
+__global__ void __launch_bounds__(1024) k_sort_tiles(SortParams S) {
     __shared__ unsigned c[kMaxSuper];
-    for (int q = threadIdx.x; q < S.nsuper; q += 256) c[q] = 0u;
+    for (int q = threadIdx.x; q < S.nsuper; q += blockDim.x) c[q] = 0u;
     __syncthreads();
-    const int64_t base = (int64_t)blockIdx.x * kSortTile;
-    for (int q = threadIdx.x; q < kSortTile; q += 256) {
+    const int64_t base = (int64_t)blockIdx.x * S.tile;
+    for (int q = threadIdx.x; q < S.tile; q += blockDim.x) {
         const int64_t p = base + q;
         if (p < S.n) {
             const uint32_t b = sort_bucket(S, p);
@@ -1600,62 +1608,39 @@ __global__ void __launch_bounds__(256) k_sort_tiles(SortParams S) {
         }
     }
     __syncthreads();
-    for (int q = threadIdx.x; q < S.nsuper; q += 256) S.cnt[(int64_t)q * S.ptiles + blockIdx.x] = c[q];
-}
-
-// Exclusive prefix sum of the tile counts (super-bucket-major) in three passes: within each tile
-// of kScanTile entries (tile totals to S.part), over the tile totals (one workgroup), then each
-// tile adds the total of the tiles before it.  Counts and sums stay below n < 2^31.
-__global__ void __launch_bounds__(kScanBlock) k_sort_scan_tiles(SortParams S) {
-    __shared__ int64_t part[kScanBlock];
-    const int64_t base = (int64_t)blockIdx.x * kScanTile + (int64_t)threadIdx.x * kScanPer;
-    unsigned v[kScanPer];
-    int64_t sum = 0;
-#pragma unroll
-    for (int q = 0; q < kScanPer; ++q) {
-        v[q] = (base + q < S.ncnt) ? S.cnt[base + q] : 0u;
-        sum += v[q];
-    }
-    const int64_t incl = block_scan(part, sum);
-    int64_t run = incl - sum;
-#pragma unroll
-    for (int q = 0; q < kScanPer; ++q) {
-        if (base + q < S.ncnt) S.cnt[base + q] = (unsigned)run;
-        run += v[q];
-    }
-    if (threadIdx.x == kScanBlock - 1) S.part[blockIdx.x] = (unsigned)incl;
-}
-
-__global__ void __launch_bounds__(kScanBlock) k_sort_scan_partials(SortParams S) {
-    __shared__ int64_t part[kScanBlock];
-    const int per = (S.ntiles + kScanBlock - 1) / kScanBlock;
-    const int lo = (int)threadIdx.x * per;
-    const int hi = (lo + per < S.ntiles) ? lo + per : S.ntiles;
-    int64_t sum = 0;
-    for (int q = lo; q < hi; ++q) sum += S.part[q];
-    int64_t run = block_scan(part, sum) - sum;
-    for (int q = lo; q < hi; ++q) {
-        const unsigned h = S.part[q];
-        S.part[q] = (unsigned)run;
-        run += h;
+    for (int q = threadIdx.x; q < S.nsuper; q += blockDim.x) {
+        const unsigned v = c[q];
+        if (v) S.cnt[(int64_t)blockIdx.x * S.nsuper + q] = atomicAdd(&S.total[q], v);
     }
 }
 
-__global__ void __launch_bounds__(kScanBlock) k_sort_scan_add(SortParams S) {
-    const unsigned add = S.part[blockIdx.x];
-    const int64_t base = (int64_t)blockIdx.x * kScanTile;
-    for (int64_t q = threadIdx.x; q < kScanTile; q += kScanBlock)
-        if (base + q < S.ncnt) S.cnt[base + q] += add;
+// The first slot of each super-bucket, into at[0 .. nsuper): every block sums the totals itself.
+__device__ __forceinline__ void super_starts(const SortParams& S, unsigned* at, unsigned* part) {
+    const int per = (S.nsuper + (int)blockDim.x - 1) / (int)blockDim.x;
+    const int q0 = (int)threadIdx.x * per;
+    const int q1 = (q0 + per < S.nsuper) ? q0 + per : S.nsuper;
+    unsigned sum = 0u;
+    for (int q = q0; q < q1; ++q) sum += S.total[q];
+    unsigned run = block_scan<unsigned>(part, sum) - sum;
+    for (int q = q0; q < q1; ++q) {
+        const unsigned v = S.total[q];
+        at[q] = run;
+        run += v;
+    }
 }
 
 // Level 1, placement: each tile writes its particles (index and bucket) from the first slot of
 // its share of each super-bucket on, ranked by LDS atomics.
-__global__ void __launch_bounds__(256) k_sort_spread(SortParams S) {
+__global__ void __launch_bounds__(1024) k_sort_spread(SortParams S) {
     __shared__ unsigned at[kMaxSuper];
-    for (int q = threadIdx.x; q < S.nsuper; q += 256) at[q] = S.cnt[(int64_t)q * S.ptiles + blockIdx.x];
+    __shared__ unsigned part[16];
+    super_starts(S, at, part);
     __syncthreads();
-    const int64_t base = (int64_t)blockIdx.x * kSortTile;
-    for (int q = threadIdx.x; q < kSortTile; q += 256) {
+    // entries of super-buckets that the tile does not hold are never read
+    for (int q = threadIdx.x; q < S.nsuper; q += blockDim.x) at[q] += S.cnt[(int64_t)blockIdx.x * S.nsuper + q];
+    __syncthreads();
+    const int64_t base = (int64_t)blockIdx.x * S.tile;
+    for (int q = threadIdx.x; q < S.tile; q += blockDim.x) {
         const int64_t p = base + q;
         if (p < S.n) {
             const uint32_t b = S.bucket[p];
@@ -1670,10 +1655,18 @@ __global__ void __launch_bounds__(256) k_sort_spread(SortParams S) {
 // its `fine` buckets, the histogram's exclusive prefix sum, then LDS-atomic ranks.
 __global__ void __launch_bounds__(kFineBlock) k_sort_fine(SortParams S) {
     __shared__ unsigned h[kFineMax];
-    __shared__ int64_t part[kFineBlock];
+    __shared__ unsigned part[16];
+    __shared__ unsigned range[2];
     const int s = blockIdx.x;
-    const int64_t lo = S.cnt[(int64_t)s * S.ptiles];
-    const int64_t hi = (s + 1 < S.nsuper) ? (int64_t)S.cnt[(int64_t)(s + 1) * S.ptiles] : S.n;
+    super_starts(S, h, part);
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        range[0] = h[s];
+        range[1] = h[s] + S.total[s];
+    }
+    __syncthreads();
+    const int64_t lo = range[0], hi = range[1];
+    if (lo == hi) return;   // uniform: an empty super-bucket
     const uint32_t b0 = (uint32_t)s * (uint32_t)S.fine;
     for (int q = threadIdx.x; q < S.fine; q += kFineBlock) h[q] = 0u;
     __syncthreads();
@@ -1683,12 +1676,12 @@ __global__ void __launch_bounds__(kFineBlock) k_sort_fine(SortParams S) {
     const int per = (S.fine + kFineBlock - 1) / kFineBlock;
     const int q0 = (int)threadIdx.x * per;
     const int q1 = (q0 + per < S.fine) ? q0 + per : S.fine;
-    int64_t sum = 0;
+    unsigned sum = 0u;
     for (int q = q0; q < q1; ++q) sum += h[q];
-    int64_t run = block_scan(part, sum) - sum;
+    unsigned run = block_scan<unsigned>(part, sum) - sum;
     for (int q = q0; q < q1; ++q) {
         const unsigned v = h[q];
-        h[q] = (unsigned)run;
+        h[q] = run;
         run += v;
     }
     __syncthreads();
@@ -1705,7 +1698,7 @@ __global__ void __launch_bounds__(kFineBlock) k_sort_fine(SortParams S) {
 
 // Tile b (kScanTile elements): scan within the tile, tile total to part[b].
 __global__ void __launch_bounds__(kScanBlock) k_scan_tiles(ScanParams S) {
-    __shared__ int64_t part[kScanBlock];
+    __shared__ int64_t part[kScanBlock / 64];
     const int64_t base = (int64_t)blockIdx.x * kScanTile + (int64_t)threadIdx.x * kScanPer;
     int64_t v[kScanPer];
     int64_t sum = 0;
@@ -1714,7 +1707,7 @@ __global__ void __launch_bounds__(kScanBlock) k_scan_tiles(ScanParams S) {
         v[q] = (base + q < S.n) ? S.v[base + q] : 0;
         sum += v[q];
     }
-    const int64_t incl = block_scan(part, sum);
+    const int64_t incl = block_scan<int64_t>(part, sum);
     int64_t run = incl - sum;
 #pragma unroll
     for (int q = 0; q < kScanPer; ++q) {
@@ -1726,13 +1719,13 @@ __global__ void __launch_bounds__(kScanBlock) k_scan_tiles(ScanParams S) {
 
 // One workgroup: exclusive scan of the tile totals; writes the leading zero.
 __global__ void __launch_bounds__(kScanBlock) k_scan_partials(ScanParams S) {
-    __shared__ int64_t part[kScanBlock];
+    __shared__ int64_t part[kScanBlock / 64];
     const int64_t per = (S.ntiles + kScanBlock - 1) / kScanBlock;
     const int64_t lo = (int64_t)threadIdx.x * per;
     const int64_t hi = (lo + per < S.ntiles) ? lo + per : S.ntiles;
     int64_t sum = 0;
     for (int64_t q = lo; q < hi; ++q) sum += S.part[q];
-    int64_t run = block_scan(part, sum) - sum;
+    int64_t run = block_scan<int64_t>(part, sum) - sum;
     for (int64_t q = lo; q < hi; ++q) {
         const int64_t h = S.part[q];
         S.part[q] = run;
@@ -1907,9 +1900,6 @@ const void* reset_kernel() { return reinterpret_cast<const void*>(&k_reset); }
 const void* fill_kernel() { return reinterpret_cast<const void*>(&k_fill); }
 const void* counts_kernel() { return reinterpret_cast<const void*>(&k_counts); }
 const void* sort_tiles_kernel() { return reinterpret_cast<const void*>(&k_sort_tiles); }
-const void* sort_scan_tiles_kernel() { return reinterpret_cast<const void*>(&k_sort_scan_tiles); }
-const void* sort_scan_partials_kernel() { return reinterpret_cast<const void*>(&k_sort_scan_partials); }
-const void* sort_scan_add_kernel() { return reinterpret_cast<const void*>(&k_sort_scan_add); }
 const void* sort_spread_kernel() { return reinterpret_cast<const void*>(&k_sort_spread); }
 const void* sort_fine_kernel() { return reinterpret_cast<const void*>(&k_sort_fine); }
 const void* scan_tiles_kernel() { return reinterpret_cast<const void*>(&k_scan_tiles); }
