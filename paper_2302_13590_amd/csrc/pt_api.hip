@@ -125,9 +125,11 @@ struct pt_run {
     hipStream_t stream;
     Counters* d_counters = nullptr;
     Counters* h_counters = nullptr;     // pinned
-    hipEvent_t ev0 = nullptr, ev1 = nullptr, ev_done = nullptr;
+    hipEvent_t ev0 = nullptr, ev1 = nullptr;     // around the call; ev1 is also its completion
     hipEvent_t evk0 = nullptr, evk1 = nullptr;   // around the tracking kernel alone
     bool launched = false;
+    bool cleared = false;               // d_counters were cleared by an earlier run's last kernel
+    bool tracks = false;                // the call has a tracking kernel
     int sched = 0, layout = 0, block = 0, grid = 0;
     // per-run device tables (batched runs, snapshot times) and their pinned staging
     void* d_tables = nullptr;
@@ -159,7 +161,6 @@ void destroy_run(pt_run* r) {
     if (r->graph) (void)hipGraphDestroy(r->graph);
     if (r->ev0) (void)hipEventDestroy(r->ev0);
     if (r->ev1) (void)hipEventDestroy(r->ev1);
-    if (r->ev_done) (void)hipEventDestroy(r->ev_done);
     if (r->evk0) (void)hipEventDestroy(r->evk0);
     if (r->evk1) (void)hipEventDestroy(r->evk1);
     if (r->d_counters) (void)hipFree(r->d_counters);
@@ -188,10 +189,9 @@ int new_run(int device, pt_run** out) {
     r->magic = kRunMagic;
     r->device = device;
     hipError_t e = hipMalloc(&r->d_counters, sizeof(Counters));
-    if (e == hipSuccess) e = hipHostMalloc(&r->h_counters, sizeof(Counters), hipHostMallocDefault);
+    if (e == hipSuccess) e = hipHostMalloc(&r->h_counters, sizeof(Counters), hipHostMallocCoherent);
     if (e == hipSuccess) e = hipEventCreate(&r->ev0);
     if (e == hipSuccess) e = hipEventCreate(&r->ev1);
-    if (e == hipSuccess) e = hipEventCreateWithFlags(&r->ev_done, hipEventDisableTiming);
     if (e == hipSuccess) e = hipEventCreate(&r->evk0);
     if (e == hipSuccess) e = hipEventCreate(&r->evk1);
     if (e != hipSuccess) {
@@ -603,7 +603,8 @@ void write_tables(const Plan& P, const pt_grid* const* grids, int32_t n_grids, c
 // (P.sort_bytes), d_scan (P.scan_bytes) and d_counters.
 void bind_params(const Plan& PL, const pt_grid* const* grids, int32_t n_grids, const pt_particles* p,
                  const pt_track_opts* o, unsigned char* d_tables, unsigned char* d_sort, int64_t* d_scan,
-                 unsigned char* d_recheck, Counters* d_counters, TrackParams& P, SortParams& SP, ScanParams& SC) {
+                 unsigned char* d_recheck, Counters* d_counters, Counters* h_counters, int64_t* counts, TrackParams& P,
+                 SortParams& SP, ScanParams& SC) {
     std::memset(&P, 0, sizeof P);
     std::memset(&SP, 0, sizeof SP);
     std::memset(&SC, 0, sizeof SC);
@@ -647,6 +648,9 @@ void bind_params(const Plan& PL, const pt_grid* const* grids, int32_t n_grids, c
     P.snap_xyz = PL.ts ? o->snap_xyz : nullptr;
     P.out_xyz = o->out_xyz;
     P.counters = d_counters;
+    P.host_counters = h_counters;
+    P.counts = counts;
+    P.path_pass = PL.path ? (PL.path_count ? 1 : 2) : 0;
     if (PL.recheck_cap > 0) {
         P.recheck_pid = reinterpret_cast<int32_t*>(d_recheck);
         P.recheck_cap = PL.recheck_cap;
@@ -720,11 +724,12 @@ ResetParams reset_params(Counters* c, const SortParams& SP) {
     return R;
 }
 
-// Counter reset, ordering sort, tracking kernel, pathline offset scan.  The argument blocks
+// Counter reset (where needed), ordering sort, tracking kernel, careful pass or publication of the
+// counters, pathline offset scan.  The argument blocks
 // are referenced, not copied: they must outlive the launches (or graph construction).
-void build_seq(const Plan& PL, int64_t n, ResetParams* RP, TrackParams* P, SortParams* SP, ScanParams* SC,
+void build_seq(const Plan& PL, int64_t n, bool reset, ResetParams* RP, TrackParams* P, SortParams* SP, ScanParams* SC,
                LaunchSeq& seq) {
-    seq.push(reset_kernel(), dim3(1), dim3(256), RP, sizeof *RP);
+    if (reset || PL.sort) seq.push(reset_kernel(), dim3(1), dim3(256), RP, sizeof *RP);
     if (n > 0) {
         if (PL.sort) {
             const unsigned nt = (unsigned)SP->ptiles, threads = (unsigned)std::min(1024, SP->tile / kSortPer);
@@ -741,6 +746,9 @@ void build_seq(const Plan& PL, int64_t n, ResetParams* RP, TrackParams* P, SortP
             seq.push(careful_kernel(PL.key), dim3(ct), dim3(cb), P, sizeof *P,
                      P->path_stage ? sizeof(PathStage) * cb : 0);
         }
+    }
+    if (PL.recheck_cap == 0) seq.push(publish_kernel(), dim3(1), dim3(64), P, sizeof *P);
+    if (n > 0) {
         if (PL.path_count)
             seq.push(scan_tiles_kernel(), dim3((unsigned)SC->ntiles), dim3(kScanBlock), SC, sizeof *SC);
     }
@@ -1138,12 +1146,15 @@ int pt_track(const pt_grid* const* grids, int32_t n_grids, const pt_particles* p
     ScanParams SC;
     bind_params(PL, grids, n_grids, p, o, static_cast<unsigned char*>(r->d_tables),
                 static_cast<unsigned char*>(r->d_sort), static_cast<int64_t*>(r->d_scan),
-                static_cast<unsigned char*>(r->d_recheck), r->d_counters, P, SP, SC);
+                static_cast<unsigned char*>(r->d_recheck), r->d_counters, r->h_counters, nullptr, P, SP, SC);
     ResetParams RP = reset_params(r->d_counters, SP);
     LaunchSeq seq;
-    build_seq(PL, p->n, &RP, &P, &SP, &SC, seq);
-
-    hipError_t e = hipEventRecord(r->ev0, s);
+    // a graph always resets: its launches do not depend on the run's history
+    build_seq(PL, p->n, o->use_graph || !r->cleared, &RP, &P, &SP, &SC, seq);
+    r->tracks = seq.track_at >= 0;
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    hipError_t e = hipStreamIsCapturing(s, &cap);
+    if (e == hipSuccess) e = hipEventRecord(r->ev0, s);
     if (e == hipSuccess) {
         if (o->use_graph) {
             // key: every launch's function, shape, dynamic LDS and argument bytes
@@ -1192,12 +1203,6 @@ int pt_track(const pt_grid* const* grids, int32_t n_grids, const pt_particles* p
                         prev = ev;
                     }
                 }
-                // no tracking kernel (no particles): both events at the end, track_ms = 0
-                for (int q = 0; e == hipSuccess && seq.track_at < 0 && q < 2; ++q) {
-                    hipGraphNode_t ev = nullptr;
-                    e = hipGraphAddEventRecordNode(&ev, gr, prev ? &prev : nullptr, prev ? 1 : 0, q ? r->evk1 : r->evk0);
-                    prev = ev;
-                }
                 if (e == hipSuccess) e = hipGraphInstantiate(&r->exec, gr, nullptr, nullptr, 0);
                 if (e == hipSuccess) {
                     r->graph = gr;
@@ -1210,17 +1215,14 @@ int pt_track(const pt_grid* const* grids, int32_t n_grids, const pt_particles* p
             if (e == hipSuccess) e = hipGraphLaunch(r->exec, s);
         } else {
             for (int q = 0; e == hipSuccess && q < seq.n; ++q) {
+                const Launch& L = seq.v[q];
                 if (q == seq.track_at) e = hipEventRecord(r->evk0, s);
-                if (e == hipSuccess) e = launch(seq.v[q].fn, seq.v[q].grid, seq.v[q].block, seq.v[q].arg, seq.v[q].lds, s);
+                if (e == hipSuccess) e = launch(L.fn, L.grid, L.block, L.arg, L.lds, s);
                 if (e == hipSuccess && q == seq.track_at) e = hipEventRecord(r->evk1, s);
             }
-            if (e == hipSuccess && seq.track_at < 0) e = hipEventRecord(r->evk0, s);
-            if (e == hipSuccess && seq.track_at < 0) e = hipEventRecord(r->evk1, s);
         }
     }
     if (e == hipSuccess) e = hipEventRecord(r->ev1, s);
-    if (e == hipSuccess) e = hipMemcpyAsync(r->h_counters, r->d_counters, sizeof(Counters), hipMemcpyDeviceToHost, s);
-    if (e == hipSuccess) e = hipEventRecord(r->ev_done, s);
     if (e != hipSuccess) {
         (void)hipGetLastError();
         (void)hipStreamSynchronize(s);
@@ -1228,6 +1230,7 @@ int pt_track(const pt_grid* const* grids, int32_t n_grids, const pt_particles* p
         return fail(hip_code(e), "launch failed: %s", hipGetErrorString(e));
     }
     r->launched = true;
+    if (cap == hipStreamCaptureStatusNone) r->cleared = true;
     add_live(r);
     *out = r;
     return PT_OK;
@@ -1258,7 +1261,7 @@ int pt_track_noalloc(const pt_grid* const* grids, int32_t n_grids, const pt_part
     SortParams SP;
     ScanParams SC;
     bind_params(PL, grids, n_grids, p, o, base + kScratchTables, base + kScratchSort,
-                reinterpret_cast<int64_t*>(base + kScratchScan), base + kScratchRecheck, cptr, P, SP, SC);
+                reinterpret_cast<int64_t*>(base + kScratchScan), base + kScratchRecheck, cptr, nullptr, counts, P, SP, SC);
     TableFill tf;
     tf.dst = base + kScratchTables;
     tf.A.nbytes = 0;
@@ -1268,12 +1271,7 @@ int pt_track_noalloc(const pt_grid* const* grids, int32_t n_grids, const pt_part
     hipError_t e = tf.err;
     LaunchSeq seq;
     ResetParams RP = reset_params(cptr, SP);
-    build_seq(PL, p->n, &RP, &P, &SP, &SC, seq);
-    CountsParams CP;
-    CP.c = cptr;
-    CP.out = counts;
-    CP.path_pass = PL.path ? (PL.path_count ? 1 : 2) : 0;
-    seq.push(counts_kernel(), dim3(1), dim3(64), &CP, sizeof CP);
+    build_seq(PL, p->n, true, &RP, &P, &SP, &SC, seq);
     for (int q = 0; e == hipSuccess && q < seq.n; ++q)
         e = launch(seq.v[q].fn, seq.v[q].grid, seq.v[q].block, seq.v[q].arg, seq.v[q].lds, s);
     if (e != hipSuccess) {
@@ -1287,11 +1285,11 @@ int pt_results(pt_run* r, pt_summary* out) {
     g_err.clear();
     if (!r || !is_live(r, kRunMagic)) return fail(PT_ERR_BAD_HANDLE, "not a live run handle");
     if (!out) return fail(PT_ERR_INVALID_ARG, "out must not be NULL");
-    HIP_TRY(hipEventSynchronize(r->ev_done));
+    HIP_TRY(hipEventSynchronize(r->ev1));
     float ms = 0.0f;
     HIP_TRY(hipEventElapsedTime(&ms, r->ev0, r->ev1));
     float kms = 0.0f;
-    HIP_TRY(hipEventElapsedTime(&kms, r->evk0, r->evk1));
+    if (r->tracks) HIP_TRY(hipEventElapsedTime(&kms, r->evk0, r->evk1));
     std::memset(out, 0, sizeof *out);
     const Counters& c = *r->h_counters;
     out->crossings = (int64_t)c.crossings;
@@ -1378,7 +1376,7 @@ int pt_release(void* h) {
         return PT_OK;
     }
     pt_run* r = static_cast<pt_run*>(h);
-    hipError_t e = hipEventSynchronize(r->ev_done);
+    hipError_t e = hipEventSynchronize(r->ev1);
     if (e != hipSuccess) {
         (void)hipGetLastError();
         destroy_run(r);

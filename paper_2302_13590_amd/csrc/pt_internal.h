@@ -79,7 +79,8 @@ struct GridDev {
 constexpr int kXcd = 8;   // accelerator complex dies; workgroup b runs on die b mod 8
 constexpr int kDieChunk = 16;   // static kernel: consecutive blocks of work dealt to one die at a time
 
-// Counters of a run (device), cleared by the reset kernel.
+// Counters of a run (device).  The kernel that publishes them clears them for the next run; the
+// reset kernel does where that is not known to have happened.
 struct Counters {
     unsigned long long crossings;
     unsigned long long status[8];
@@ -87,7 +88,8 @@ struct Counters {
     unsigned long long queue[kXcd];   // next slot handed out in each die's segment
     unsigned long long path_dropped;  // pathline records outside their slot range
     unsigned long long recheck_tracks;  // particles handed to the careful pass (may exceed its capacity)
-    unsigned long long pad[12];
+    unsigned long long done;            // careful pass: blocks that have finished
+    unsigned long long pad[11];
 };
 static_assert(sizeof(Counters) == 32 * 8, "Counters is 32 words");
 
@@ -154,7 +156,11 @@ struct TrackParams {
     // tracked again from its input state by the careful kernel.
     int32_t* recheck_pid;
     int32_t recheck_cap;          // entries of recheck_pid (0: no careful pass)
-    int32_t pad_recheck;
+    // Where the counters go at the end of the call: the run's pinned host block (pt_track), or the
+    // caller's device counts in the layout of PT_COUNT_* (pt_track_noalloc).
+    int32_t path_pass;            // 0: none, 1: count pass, 2: record pass
+    Counters* host_counters;
+    int64_t* counts;
 };
 
 // Output form of a tracking kernel (template argument).
@@ -278,14 +284,8 @@ struct FillArgs {
     uint32_t pad;
     unsigned char bytes[2048];
 };
-struct CountsParams {
-    const Counters* c;
-    int64_t* out;          // PT_COUNTS_WORDS int64, device
-    int32_t path_pass;     // 0: none, 1: count pass, 2: record pass
-    int32_t pad;
-};
 const void* fill_kernel();
-const void* counts_kernel();
+const void* publish_kernel();
 
 constexpr int kMaxSnapLds = 1024;
 
