@@ -79,7 +79,10 @@ extern "C" {
 #define PT_MIXED 1             /* in-cell arithmetic in FP32; time, global position and the    *
                                 * near-zero-gradient branch in FP64                            */
 
-#define PT_SCHED_AUTO 0
+#define PT_SCHED_AUTO 0        /* the static kernel for ordered work and for what the GPU      *
+                                * holds at once twice over (FP64 on structured grids: four     *
+                                * threads per particle, one per axis, up to 128 particles per  *
+                                * compute unit when block is 0), else the persistent kernel    */
 #define PT_SCHED_STATIC 1      /* one thread per particle for its whole track                 */
 #define PT_SCHED_PERSISTENT 2  /* resident waves pull particles from a device work queue and   *
                                 * refill finished lanes (wave-level compaction)               */

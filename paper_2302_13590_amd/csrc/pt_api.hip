@@ -437,6 +437,7 @@ struct Plan {
     const void* fn = nullptr;
     bool ts = false, path = false, path_count = false, transient = false, batched = false, multi = false;
     bool sort = false;
+    bool axes = false;              // four lanes per particle (k_track_axes)
     int32_t n_groups = 0;
     int block = 0, grid = 0;
     size_t lds = 0;                 // dynamic LDS of the tracking kernel
@@ -517,9 +518,16 @@ int make_plan(const pt_grid* const* grids, int32_t n_grids, const pt_particles* 
     const int64_t resident = (int64_t)n_cu * 4 * 64 * waves_static(P.key.precision, P.key.out);
     if (o->schedule == PT_SCHED_AUTO) P.key.sched = (P.sort || p->n <= 2 * resident) ? S_STATIC : S_PERSISTENT;
     else P.key.sched = o->schedule == PT_SCHED_STATIC ? S_STATIC : S_PERSISTENT;
-    P.fn = track_kernel(P.key);
+    // With the launch left to the library, few particles are tracked by four lanes each: while that
+    // makes at most two waves per SIMD, i.e. up to 128 particles per compute unit.
+    P.axes = o->schedule == PT_SCHED_AUTO && o->block == 0 && P.key.sched == S_STATIC && P.key.precision == P64 &&
+             P.key.layout == L_CELL && p->n <= (int64_t)128 * n_cu;
+    P.fn = P.axes ? axes_kernel(P.key) : track_kernel(P.key);
     P.block = o->block;
-    if (P.key.sched == S_STATIC) {
+    if (P.axes) {
+        P.block = 64;   // 16 particles: as many compute units as the call can use
+        P.grid = (int)std::max<int64_t>(1, (p->n + 15) / 16);
+    } else if (P.key.sched == S_STATIC) {
         // Default block.  One wave when the particles give each compute unit at most one (a block
         // of four would leave compute units idle: 4,096 particles 275 / 286 us), and when each
         // lane's place is taken eight times or more (no wave waits for its block's slowest: 4e6 with
@@ -559,9 +567,9 @@ int make_plan(const pt_grid* const* grids, int32_t n_grids, const pt_particles* 
     }
     // the static timeseries kernels on packed layouts keep one deferred-snapshot slot per thread
     // in dynamic LDS; the pathline record pass stages each lane's records there
-    const bool snap_slots = P.key.out == O_SERIES && P.key.sched == S_STATIC && P.key.layout != L_FACES;
+    const bool snap_slots = P.key.out == O_SERIES && P.key.sched == S_STATIC && P.key.layout != L_FACES && !P.axes;
     const size_t slot = P.key.precision == P64 ? sizeof(SnapJob<double>) : sizeof(SnapJob<float>);
-    const bool stage = P.path && !P.path_count && (reinterpret_cast<uintptr_t>(o->path_records) % 64 == 0);
+    const bool stage = P.path && !P.path_count && !P.axes && (reinterpret_cast<uintptr_t>(o->path_records) % 64 == 0);
     P.lds = snap_slots ? slot * (size_t)P.block : (stage ? sizeof(PathStage) * (size_t)P.block : 0);
     return PT_OK;
 }
@@ -665,7 +673,7 @@ void bind_params(const Plan& PL, const pt_grid* const* grids, int32_t n_grids, c
             P.path_cap = o->path_cap;
             P.path_rec = reinterpret_cast<PathRec*>(o->path_records);
             // staged record writes need 64-byte aligned segments of the record array
-            P.path_stage = (reinterpret_cast<uintptr_t>(o->path_records) % 64 == 0) ? 1 : 0;
+            P.path_stage = (!PL.axes && reinterpret_cast<uintptr_t>(o->path_records) % 64 == 0) ? 1 : 0;
         }
     }
     if (PL.path_count) {   // the per-particle counts become offsets (scan of path_offsets[1..n])

@@ -233,6 +233,7 @@ struct KernelKey {
 
 // Kernel lookup (defined in pt_kernels.hip).
 const void* track_kernel(const KernelKey& k);
+const void* axes_kernel(const KernelKey& k);           // FP64, packed structured records
 const void* careful_kernel(const KernelKey& k);        // FP64 keys only
 const void* reset_kernel();
 const void* sort_tiles_kernel();
