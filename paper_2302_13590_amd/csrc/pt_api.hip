@@ -438,6 +438,7 @@ struct Plan {
     bool ts = false, path = false, path_count = false, transient = false, batched = false, multi = false;
     bool sort = false;
     bool axes = false;              // four lanes per particle (k_track_axes)
+    bool stage = false;             // pathline record pass: records staged in LDS
     int32_t n_groups = 0;
     int block = 0, grid = 0;
     size_t lds = 0;                 // dynamic LDS of the tracking kernel
@@ -569,8 +570,12 @@ int make_plan(const pt_grid* const* grids, int32_t n_grids, const pt_particles* 
     // in dynamic LDS; the pathline record pass stages each lane's records there
     const bool snap_slots = P.key.out == O_SERIES && P.key.sched == S_STATIC && P.key.layout != L_FACES && !P.axes;
     const size_t slot = P.key.precision == P64 ? sizeof(SnapJob<double>) : sizeof(SnapJob<float>);
-    const bool stage = P.path && !P.path_count && !P.axes && (reinterpret_cast<uintptr_t>(o->path_records) % 64 == 0);
-    P.lds = snap_slots ? slot * (size_t)P.block : (stage ? sizeof(PathStage) * (size_t)P.block : 0);
+    // Staged record writes: 64-byte segments of an aligned record array, against writing each record
+    // where it belongs.  Staging pays when the writes fill the memory (2e5 particles 775 / 1007 us,
+    // 1e6 2.12 / 2.93 ms); up to a wave per SIMD its instructions cost more (50,000 383 / 332 us).
+    P.stage = P.path && !P.path_count && !P.axes && p->n > (int64_t)256 * n_cu &&
+              (reinterpret_cast<uintptr_t>(o->path_records) % 64 == 0);
+    P.lds = snap_slots ? slot * (size_t)P.block : (P.stage ? sizeof(PathStage) * (size_t)P.block : 0);
     return PT_OK;
 }
 
@@ -672,8 +677,7 @@ void bind_params(const Plan& PL, const pt_grid* const* grids, int32_t n_grids, c
         if (!PL.path_count) {
             P.path_cap = o->path_cap;
             P.path_rec = reinterpret_cast<PathRec*>(o->path_records);
-            // staged record writes need 64-byte aligned segments of the record array
-            P.path_stage = (!PL.axes && reinterpret_cast<uintptr_t>(o->path_records) % 64 == 0) ? 1 : 0;
+            P.path_stage = PL.stage ? 1 : 0;
         }
     }
     if (PL.path_count) {   // the per-particle counts become offsets (scan of path_offsets[1..n])
