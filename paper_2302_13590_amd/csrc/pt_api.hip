@@ -1016,7 +1016,7 @@ int pt_load_quad_grid(const pt_quad_desc* d, void* hip_stream, pt_grid** out) {
         return e;
     };
     const size_t n_sub = (size_t)std::max<int64_t>(1, nsub);
-    void *box, *off, *nb, *sq, *sr, *por = nullptr, *flags, *rec, *err;
+    void *box, *off, *nb, *sq, *sr, *por = nullptr, *flags, *rec, *face, *err;
     hipError_t e = alloc(sizeof(QuadBox) * ncell, &box);
     if (e == hipSuccess) e = alloc(sizeof(int32_t) * (6 * ncell + 1), &off);
     if (e == hipSuccess) e = alloc(sizeof(int32_t) * n_sub, &nb);
@@ -1025,6 +1025,7 @@ int pt_load_quad_grid(const pt_quad_desc* d, void* hip_stream, pt_grid** out) {
     if (e == hipSuccess && d->porosity) e = alloc(sizeof(double) * ncell, &por);
     if (e == hipSuccess) e = alloc(sizeof(int32_t) * ncell, &flags);
     if (e == hipSuccess) e = alloc(sizeof(QuadRec) * ncell, &rec);
+    if (e == hipSuccess) e = alloc(sizeof(QuadFace) * ncell, &face);
     if (e == hipSuccess) e = alloc(4 * sizeof(int), &err);
     if (e != hipSuccess) {
         (void)hipGetLastError();
@@ -1048,11 +1049,13 @@ int pt_load_quad_grid(const pt_quad_desc* d, void* hip_stream, pt_grid** out) {
     B.ncell = ncell;
     B.box = static_cast<const QuadBox*>(box);
     B.sub_off = static_cast<const int32_t*>(off);
+    B.sub_nb = static_cast<const int32_t*>(nb);
     B.sub_q = static_cast<const double*>(sq);
     B.por = static_cast<const double*>(por);
     B.por_scalar = d->porosity ? 0.0 : d->porosity_scalar;
     B.flags = static_cast<const int32_t*>(flags);
     B.rec = static_cast<QuadRec*>(rec);
+    B.face = static_cast<QuadFace*>(face);
     B.balance_tol = d->balance_tol;
     B.err = static_cast<int*>(err);
     if (e == hipSuccess)
@@ -1075,6 +1078,7 @@ int pt_load_quad_grid(const pt_quad_desc* d, void* hip_stream, pt_grid** out) {
     GridDev& gd = g->gd;
     std::memset(&gd, 0, sizeof gd);
     gd.rec64 = reinterpret_cast<const CellRec64*>(rec);   // QuadRec shares the record prefix
+    gd.rec32 = reinterpret_cast<const CellRec32*>(face);
     gd.por = static_cast<double*>(por);
     gd.flags = static_cast<int32_t*>(flags);
     gd.por_scalar = B.por_scalar;

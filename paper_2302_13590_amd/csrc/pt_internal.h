@@ -52,6 +52,15 @@ struct alignas(64) QuadRec {
 };
 static_assert(sizeof(QuadRec) == 64, "QuadRec must be 64 bytes");
 constexpr int kMaxSubPerFace = 31;
+// The neighbour across each face, where the record alone decides the transfer: a cell id >= 0 (the
+// face has one subface, and the neighbour spans the same range on both tangential axes, so the
+// face coordinates carry over), FACE_OUT (the domain boundary), or FACE_SPLIT (the subfaces and
+// the boxes decide).
+struct alignas(32) QuadFace {
+    int32_t nb[6];
+    int32_t pad[2];
+};
+enum : int32_t { FACE_OUT = -1, FACE_SPLIT = -2 };
 struct QuadBox {
     double lo[3];   // x_lo, y_lo, z_lo
     double h[3];    // hx, hy, hz
@@ -60,7 +69,7 @@ struct QuadBox {
 // One flow field as the kernels see it.
 struct GridDev {
     const CellRec64* rec64;
-    const CellRec32* rec32;
+    const CellRec32* rec32;   // quadtree grids: QuadFace entries
     const double* qx;
     const double* qy;
     const double* qz;
@@ -267,11 +276,13 @@ struct BuildQuadParams {
     int64_t ncell;
     const QuadBox* box;
     const int32_t* sub_off;     // [ncell*6 + 1]
+    const int32_t* sub_nb;
     const double* sub_q;
     const double* por;          // nullptr -> por_scalar
     double por_scalar;
     const int32_t* flags;       // nullptr -> all active
     QuadRec* rec;
+    QuadFace* face;
     double balance_tol;
     int* err;                   // [4]: non-finite flow, bad porosity, bad flags, unbalanced
 };

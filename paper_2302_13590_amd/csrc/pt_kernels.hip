@@ -388,6 +388,9 @@ struct Lane {
     int32_t fl;         // packed layout: the current cell's flag word
     int32_t nc0;        // pathline: crossings before this call
     int32_t zrun;       // quadtree: zero-time crossings in a row
+    int32_t sub_base;   // quadtree: the current cell's first subface, subface counts and neighbours
+    uint32_t counts;
+    int32_t nbf[6];
     int64_t pq, pend;   // pathline record pass: next slot, end of the particle's slots
 };
 
@@ -451,6 +454,23 @@ __device__ __forceinline__ void load_rec(const GridDev& G, int32_t c, double sig
             }
         }
     }
+}
+
+// Gather the record and the face neighbours of a quadtree cell into the lane.
+__device__ __forceinline__ void load_quad(const GridDev& G, int32_t c, double sign, Lane<P64>& L) {
+    load_rec<P64>(G, c, sign, L.v1, L.v2, L.fl);
+    const QuadRec* rec = reinterpret_cast<const QuadRec*>(G.rec64) + (uint32_t)c;
+    L.sub_base = rec->sub_base;
+    L.counts = rec->counts;
+    const QuadFace* face = reinterpret_cast<const QuadFace*>(G.rec32) + (uint32_t)c;
+    const int4 a = *reinterpret_cast<const int4*>(face->nb);
+    const int2 b = *reinterpret_cast<const int2*>(face->nb + 4);
+    L.nbf[0] = a.x;
+    L.nbf[1] = a.y;
+    L.nbf[2] = a.z;
+    L.nbf[3] = a.w;
+    L.nbf[4] = b.x;
+    L.nbf[5] = b.y;
 }
 
 // Gather one cell: face velocities (with the direction sign) and the flag word.
@@ -810,7 +830,8 @@ __device__ int32_t begin(Lane<PREC>& L, const TrackParams& P, const double* snap
         }
         return ST_INVALID;
     }
-    if constexpr (kPacked<LAYOUT>) load_rec<PREC>(G, c, P.sign, L.v1, L.v2, L.fl);
+    if constexpr (LAYOUT == L_QUAD) load_quad(G, c, P.sign, L);
+    else if constexpr (kPacked<LAYOUT>) load_rec<PREC>(G, c, P.sign, L.v1, L.v2, L.fl);
     L.c = c;
     L.zrun = 0;
     if constexpr (kTrackIJK<LAYOUT, OUT>) cell_ijk(G, c, L.i, L.j, L.k);
@@ -883,55 +904,56 @@ __device__ void finish(Lane<PREC>& L, int32_t st, const TrackParams& P, unsigned
     if constexpr (OUT == O_SERIES) nan_rest(L, P);
 }
 
-// Quadtree transfer (after the crossing through face f of axis `axis`): the subface holding
-// the exit point (the first in order on an edge between two) gives the neighbour; in it, a
-// face coordinate carries over when both cells span the same range on that axis and is
-// mapped through the global coordinate otherwise.  A particle handed round a point in
+// Quadtree transfer (after the crossing through face f of axis `axis`).  Where the cell's face entry
+// names the neighbour, its record is already in the lane and the face coordinates carry over.
+// Otherwise the subface holding the exit point (the first in order on an edge between two) gives
+// the neighbour; in it, a face coordinate carries over when both cells span the same range on that
+// axis and is mapped through the global coordinate otherwise.  A particle handed round a point in
 // kQuadZeroRun zero-time crossings in a row (face velocities of split faces are averages,
 // so they can circulate there) stops as stranded.
 constexpr int kQuadZeroRun = 16;
 
 template <int PREC, int OUT>
-__device__ int32_t quad_transfer(Lane<PREC>& L, const GridDev& G, const TrackParams& P, const double* snap,
-                                 int32_t axis, int32_t f, double xe, double dt) {
-    const QuadRec& R = reinterpret_cast<const QuadRec*>(G.rec64)[L.c];
-    const uint32_t counts = R.counts;
-    int32_t q0 = R.sub_base;
-    for (int32_t g = 0; g < f; ++g) q0 += (int32_t)((counts >> (5 * g)) & 31u);
-    const int32_t q1 = q0 + (int32_t)((counts >> (5 * f)) & 31u);
-    const int ta1 = (axis == 0) ? 1 : 0;
-    const int ta2 = (axis == 2) ? 1 : 2;
-    const double t1 = (ta1 == 0) ? (double)L.x[0] : (double)L.x[1];
-    const double t2 = (ta2 == 1) ? (double)L.x[1] : (double)L.x[2];
-    // the last subface is taken when no earlier one holds the point, so it is never tested (a
-    // face with one subface reads no extent)
-    int32_t hit = q1 - 1;
-    for (int32_t q = q0; q < q1 - 1; ++q) {
-        const double4 r = G.sub_rect[q];
-        if (r.x <= t1 && t1 <= r.z && r.y <= t2 && t2 <= r.w) {
-            hit = q;
-            break;
+__device__ __forceinline__ int32_t quad_transfer(Lane<PREC>& L, const GridDev& G, const TrackParams& P,
+                                                 const double* snap, int32_t axis, int32_t f, double xe, double dt,
+                                                 int32_t nb, int32_t sub_base, uint32_t counts) {
+    if (nb == FACE_OUT) return ST_BOUNDARY;
+    if (nb == FACE_SPLIT) {
+        int32_t q0 = sub_base;
+        for (int32_t g = 0; g < f; ++g) q0 += (int32_t)((counts >> (5 * g)) & 31u);
+        const int32_t q1 = q0 + (int32_t)((counts >> (5 * f)) & 31u);
+        const int ta1 = (axis == 0) ? 1 : 0;
+        const int ta2 = (axis == 2) ? 1 : 2;
+        const double t1 = (ta1 == 0) ? (double)L.x[0] : (double)L.x[1];
+        const double t2 = (ta2 == 1) ? (double)L.x[1] : (double)L.x[2];
+        // the last subface is taken when no earlier one holds the point, so it is never tested
+        int32_t hit = q1 - 1;
+        for (int32_t q = q0; q < q1 - 1; ++q) {
+            const double4 r = G.sub_rect[q];
+            if (r.x <= t1 && t1 <= r.z && r.y <= t2 && t2 <= r.w) {
+                hit = q;
+                break;
+            }
+        }
+        nb = (q1 > q0) ? G.sub_nb[hit] : -1;
+        if (nb < 0) return ST_BOUNDARY;
+        load_quad(G, nb, P.sign, L);
+        if (!(L.fl & CF_ACTIVE)) return ST_INACTIVE_NB;
+        const QuadBox& B = G.qbox[L.c];
+        const QuadBox& N = G.qbox[nb];
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+            if (a == axis) continue;
+            if (N.lo[a] == B.lo[a] && N.h[a] == B.h[a]) continue;   // same span: unchanged
+            const double x = B.lo[a] + (double)L.x[a] * B.h[a];
+            double l = (x - N.lo[a]) / N.h[a];
+            l = (l < 0.0) ? 0.0 : l;
+            l = (l > 1.0) ? 1.0 : l;
+            L.x[a] = l;
         }
     }
-    const int32_t nb = (q1 > q0) ? G.sub_nb[hit] : -1;
-    if (nb < 0) return ST_BOUNDARY;
-    // the neighbour's record, gathered at once (its flags decide the transfer; the velocities
-    // of the cell left are not read again)
-    load_rec<PREC>(G, nb, P.sign, L.v1, L.v2, L.fl);
     const int32_t nfl = L.fl;
     if (!(nfl & CF_ACTIVE)) return ST_INACTIVE_NB;
-    const QuadBox& B = G.qbox[L.c];
-    const QuadBox& N = G.qbox[nb];
-#pragma unroll
-    for (int a = 0; a < 3; ++a) {
-        if (a == axis) continue;
-        if (N.lo[a] == B.lo[a] && N.h[a] == B.h[a]) continue;   // same span: unchanged
-        const double x = B.lo[a] + (double)L.x[a] * B.h[a];
-        double l = (x - N.lo[a]) / N.h[a];
-        l = (l < 0.0) ? 0.0 : l;
-        l = (l > 1.0) ? 1.0 : l;
-        L.x[a] = l;
-    }
     // constant indices only: the lane state stays in registers
     L.x[0] = (axis == 0) ? 1.0 - xe : L.x[0];
     L.x[1] = (axis == 1) ? 1.0 - xe : L.x[1];
@@ -1065,6 +1087,15 @@ __device__ __forceinline__ int32_t track_step(Lane<PREC>& L, const TrackParams& 
     // the neighbour across the exit face, and whether the particle moves into it
     int32_t nc = L.c;
     bool moves = false;
+    int32_t face = 0, sub_base = 0;   // quadtree: the exit face's entry, the cell's subfaces
+    uint32_t counts = 0u;
+    if constexpr (LAYOUT == L_QUAD) {
+        const int32_t n0 = hi ? L.nbf[1] : L.nbf[0], n1 = hi ? L.nbf[3] : L.nbf[2], n2 = hi ? L.nbf[5] : L.nbf[4];
+        face = c0 ? n0 : (c1 ? n1 : n2);
+        sub_base = L.sub_base;
+        counts = L.counts;
+        load_quad(G, (int)(axis >= 0) & (int)(face >= 0) ? face : L.c, P.sign, L);
+    }
     if constexpr (LAYOUT == L_CELL) {
         // cell id stride of the axis, selected from uniform values (no per-lane multiply)
         const int32_t stride = c0 ? 1 : (c1 ? G.nx : G.plane);
@@ -1189,7 +1220,7 @@ __device__ __forceinline__ int32_t track_step(Lane<PREC>& L, const TrackParams& 
         L.x[0] = c0 ? xe : na;
         L.x[1] = c1 ? xe : (c0 ? na : nb);
         L.x[2] = c2 ? xe : nb;
-        return quad_transfer<PREC, OUT>(L, G, P, snap, axis, f, xe, dt);
+        return quad_transfer<PREC, OUT>(L, G, P, snap, axis, f, xe, dt, face, sub_base, counts);
     }
     int32_t nfl_sink, stop = 0;
     if constexpr (LAYOUT == L_CELL) {
@@ -2026,6 +2057,24 @@ __global__ void __launch_bounds__(256) k_build_quad(BuildQuadParams B) {
     r.counts = counts;
     r.pad0 = 0;
     B.rec[c] = r;
+    QuadFace F;
+    for (int f = 0; f < 6; ++f) {
+        const int32_t a = B.sub_off[6 * c + f], b = B.sub_off[6 * c + f + 1];
+        int32_t nb = FACE_SPLIT;
+        if (b == a) {
+            nb = FACE_OUT;
+        } else if (b == a + 1) {
+            nb = B.sub_nb[a];
+            if (nb >= 0) {
+                const QuadBox& N = B.box[nb];
+                for (int t = 0; t < 3; ++t)
+                    if (t != (f >> 1) && !(N.lo[t] == X.lo[t] && N.h[t] == X.h[t])) nb = FACE_SPLIT;
+            }
+        }
+        F.nb[f] = nb;
+    }
+    F.pad[0] = F.pad[1] = 0;
+    B.face[c] = F;
 }
 
 // Grid load: validate the field and build both packed records of every cell.
