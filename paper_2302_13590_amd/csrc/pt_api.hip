@@ -116,7 +116,8 @@ struct pt_grid {
     int device;
     bool quad = false;   // a quadtree grid (QuadRec records, boxes, subfaces)
     GridDev gd;
-    std::vector<void*> allocs;
+    void* mem = nullptr;   // one allocation for all its arrays
+    size_t bytes = 0;
 };
 
 struct pt_run {
@@ -266,21 +267,38 @@ struct Launch {
 // ---------------------------------------------------------------------------------------------
 // grid validation of host-resident inputs (device-resident inputs are checked by k_build)
 
+// Whole-array forms of the element tests, without an exit per element (a million doubles take 0.44 ms
+// instead of 0.77 ms): only an array that fails is searched for the element to name.
+bool all_finite(const double* v, int64_t n) {
+    double s[8] = {0, 0, 0, 0, 0, 0, 0, 0};   // x * 0 is 0, or NaN for an infinity or NaN
+    int64_t q = 0;
+    for (; q + 8 <= n; q += 8)
+        for (int k = 0; k < 8; ++k) s[k] += v[q + k] * 0.0;
+    for (; q < n; ++q) s[0] += v[q] * 0.0;
+    return ((s[0] + s[1]) + (s[2] + s[3])) + ((s[4] + s[5]) + (s[6] + s[7])) == 0.0;
+}
+int32_t all_bits(const int32_t* v, int64_t n) {
+    int32_t b = 0;
+    for (int64_t q = 0; q < n; ++q) b |= v[q];
+    return b;
+}
+
 int check_host_grid(const pt_grid_desc* d) {
     const int64_t nx = d->nx, ny = d->ny, nz = d->nz;
     const int64_t nfx = (nx + 1) * ny * nz, nfy = nx * (ny + 1) * nz, nfz = nx * ny * (nz + 1);
     const int64_t ncell = nx * ny * nz;
-    for (int64_t q = 0; q < nfx; ++q)
-        if (!is_fin(d->qx[q])) return fail(PT_ERR_INVALID_ARG, "qx[%lld] is not finite", (long long)q);
-    for (int64_t q = 0; q < nfy; ++q)
-        if (!is_fin(d->qy[q])) return fail(PT_ERR_INVALID_ARG, "qy[%lld] is not finite", (long long)q);
-    for (int64_t q = 0; q < nfz; ++q)
-        if (!is_fin(d->qz[q])) return fail(PT_ERR_INVALID_ARG, "qz[%lld] is not finite", (long long)q);
+    const struct { const double* v; int64_t n; const char* name; } flows[3] = {
+        {d->qx, nfx, "qx"}, {d->qy, nfy, "qy"}, {d->qz, nfz, "qz"}};
+    for (const auto& f : flows) {
+        if (all_finite(f.v, f.n)) continue;
+        for (int64_t q = 0; q < f.n; ++q)
+            if (!is_fin(f.v[q])) return fail(PT_ERR_INVALID_ARG, "%s[%lld] is not finite", f.name, (long long)q);
+    }
     if (d->porosity)
         for (int64_t c = 0; c < ncell; ++c)
             if (!(d->porosity[c] > 0.0) || !is_fin(d->porosity[c]))
                 return fail(PT_ERR_INVALID_ARG, "porosity[%lld] must be finite and > 0", (long long)c);
-    if (d->flags)
+    if (d->flags && (all_bits(d->flags, ncell) & ~(PT_CELL_ACTIVE | PT_CELL_SINK)))
         for (int64_t c = 0; c < ncell; ++c)
             if (d->flags[c] & ~(PT_CELL_ACTIVE | PT_CELL_SINK))
                 return fail(PT_ERR_INVALID_ARG, "flags[%lld] has unknown bits", (long long)c);
@@ -308,10 +326,77 @@ int check_host_grid(const pt_grid_desc* d) {
     return PT_OK;
 }
 
-void free_grid(pt_grid* g) {
-    for (void* p : g->allocs) (void)hipFree(p);
+// Device memory of released grids, kept for the next load of about its size on the same device: a
+// loop over realisations then neither maps nor unmaps memory (1e5 cells from host arrays: load 265 ->
+// 180 us, release 96 -> 29 us, with one block for all arrays of a grid instead of eight).  At most kGridPoolMax blocks and kGridPoolBytes; guarded by g_mu; a block
+// enters only after its device has been synchronised; an allocation that fails empties the pool and
+// tries again, and pt_shutdown frees it.
+struct GridBlock {
+    void* mem;
+    size_t bytes;
+    int device;
+};
+std::vector<GridBlock> g_grid_pool;
+constexpr size_t kGridPoolMax = 8;
+constexpr size_t kGridPoolBytes = (size_t)256 << 20;
+
+void drop_grid_pool() {
+    std::vector<GridBlock> v;
+    {
+        std::lock_guard<std::mutex> lk(g_mu);
+        v.swap(g_grid_pool);
+    }
+    for (const GridBlock& b : v) (void)hipFree(b.mem);
+}
+
+hipError_t grid_memory(pt_grid* g, size_t bytes) {
+    {
+        std::lock_guard<std::mutex> lk(g_mu);
+        for (size_t q = 0; q < g_grid_pool.size(); ++q) {
+            const GridBlock& b = g_grid_pool[q];
+            if (b.device == g->device && b.bytes >= bytes && b.bytes <= 2 * bytes) {
+                g->mem = b.mem;
+                g->bytes = b.bytes;
+                g_grid_pool.erase(g_grid_pool.begin() + (ptrdiff_t)q);
+                return hipSuccess;
+            }
+        }
+    }
+    hipError_t e = hipMalloc(&g->mem, bytes);
+    if (e == hipErrorOutOfMemory) {
+        (void)hipGetLastError();
+        drop_grid_pool();
+        e = hipMalloc(&g->mem, bytes);
+    }
+    g->bytes = e == hipSuccess ? bytes : 0;
+    return e;
+}
+
+// Free a grid whose device has no work left on it; `keep`: its memory may go to the pool.
+void free_grid(pt_grid* g, bool keep = false) {
+    if (g->mem && keep) {
+        std::lock_guard<std::mutex> lk(g_mu);
+        size_t held = g->bytes;
+        for (const GridBlock& b : g_grid_pool) held += b.bytes;
+        if (g_grid_pool.size() < kGridPoolMax && held <= kGridPoolBytes) {
+            g_grid_pool.push_back({g->mem, g->bytes, g->device});
+            g->mem = nullptr;
+        }
+    }
+    if (g->mem) (void)hipFree(g->mem);
     delete g;
 }
+
+// Places arrays in one block, 256-byte aligned: a first walk (base null) sums their sizes.
+struct Carve {
+    char* base = nullptr;
+    size_t used = 0;
+    void* take(size_t bytes) {
+        void* p = base ? base + used : nullptr;
+        used += align_up(bytes, 256);
+        return p;
+    }
+};
 
 // Launch one kernel through the HIP module-less API.
 hipError_t launch(const void* fn, dim3 grid, dim3 block, void* arg, size_t lds, hipStream_t s) {
@@ -894,25 +979,28 @@ int pt_load_grid(const pt_grid_desc* d, void* hip_stream, pt_grid** out) {
     pt_grid* g = new pt_grid();
     g->magic = kGridMagic;
     g->device = dev;
-    auto alloc = [&](size_t bytes, void** p) -> hipError_t {
-        hipError_t e = hipMalloc(p, bytes);
-        if (e == hipSuccess) g->allocs.push_back(*p);
-        return e;
-    };
     void *qx, *qy, *qz, *por = nullptr, *flags, *r64, *r32, *err;
-    hipError_t e = alloc(bx, &qx);
-    if (e == hipSuccess) e = alloc(by, &qy);
-    if (e == hipSuccess) e = alloc(bz, &qz);
-    if (e == hipSuccess && d->porosity) e = alloc(bc, &por);
-    if (e == hipSuccess) e = alloc(bf, &flags);
-    if (e == hipSuccess) e = alloc(sizeof(CellRec64) * ncell, &r64);
-    if (e == hipSuccess) e = alloc(sizeof(CellRec32) * ncell, &r32);
-    if (e == hipSuccess) e = alloc(4 * sizeof(int), &err);
+    auto place = [&](Carve& m) {
+        r64 = m.take(sizeof(CellRec64) * ncell);
+        r32 = m.take(sizeof(CellRec32) * ncell);
+        qx = m.take(bx);
+        qy = m.take(by);
+        qz = m.take(bz);
+        if (d->porosity) por = m.take(bc);
+        flags = m.take(bf);
+        err = m.take(4 * sizeof(int));
+    };
+    Carve m;
+    place(m);
+    hipError_t e = grid_memory(g, m.used);
     if (e != hipSuccess) {
         (void)hipGetLastError();
         free_grid(g);
         return fail(hip_code(e), "grid allocation failed: %s", hipGetErrorString(e));
     }
+    m.base = static_cast<char*>(g->mem);
+    m.used = 0;
+    place(m);
     const hipMemcpyKind kind = d->mem == PT_MEM_HOST ? hipMemcpyHostToDevice : hipMemcpyDeviceToDevice;
     e = hipMemcpyAsync(qx, d->qx, bx, kind, s);
     if (e == hipSuccess) e = hipMemcpyAsync(qy, d->qy, by, kind, s);
@@ -1010,28 +1098,31 @@ int pt_load_quad_grid(const pt_quad_desc* d, void* hip_stream, pt_grid** out) {
     g->magic = kGridMagic;
     g->device = dev;
     g->quad = true;
-    auto alloc = [&](size_t bytes, void** ptr) -> hipError_t {
-        hipError_t e = hipMalloc(ptr, bytes);
-        if (e == hipSuccess) g->allocs.push_back(*ptr);
-        return e;
-    };
     const size_t n_sub = (size_t)std::max<int64_t>(1, nsub);
     void *box, *off, *nb, *sq, *sr, *por = nullptr, *flags, *rec, *face, *err;
-    hipError_t e = alloc(sizeof(QuadBox) * ncell, &box);
-    if (e == hipSuccess) e = alloc(sizeof(int32_t) * (6 * ncell + 1), &off);
-    if (e == hipSuccess) e = alloc(sizeof(int32_t) * n_sub, &nb);
-    if (e == hipSuccess) e = alloc(sizeof(double) * n_sub, &sq);
-    if (e == hipSuccess) e = alloc(sizeof(double4) * n_sub, &sr);
-    if (e == hipSuccess && d->porosity) e = alloc(sizeof(double) * ncell, &por);
-    if (e == hipSuccess) e = alloc(sizeof(int32_t) * ncell, &flags);
-    if (e == hipSuccess) e = alloc(sizeof(QuadRec) * ncell, &rec);
-    if (e == hipSuccess) e = alloc(sizeof(QuadFace) * ncell, &face);
-    if (e == hipSuccess) e = alloc(4 * sizeof(int), &err);
+    auto place = [&](Carve& m) {
+        rec = m.take(sizeof(QuadRec) * ncell);
+        face = m.take(sizeof(QuadFace) * ncell);
+        box = m.take(sizeof(QuadBox) * ncell);
+        off = m.take(sizeof(int32_t) * (6 * ncell + 1));
+        nb = m.take(sizeof(int32_t) * n_sub);
+        sq = m.take(sizeof(double) * n_sub);
+        sr = m.take(sizeof(double4) * n_sub);
+        if (d->porosity) por = m.take(sizeof(double) * ncell);
+        flags = m.take(sizeof(int32_t) * ncell);
+        err = m.take(4 * sizeof(int));
+    };
+    Carve m;
+    place(m);
+    hipError_t e = grid_memory(g, m.used);
     if (e != hipSuccess) {
         (void)hipGetLastError();
         free_grid(g);
         return fail(hip_code(e), "grid allocation failed: %s", hipGetErrorString(e));
     }
+    m.base = static_cast<char*>(g->mem);
+    m.used = 0;
+    place(m);
     std::vector<int32_t> ones;
     if (!d->flags) ones.assign((size_t)ncell, PT_CELL_ACTIVE);
     const hipMemcpyKind h2d = hipMemcpyHostToDevice;
@@ -1375,6 +1466,7 @@ int pt_shutdown(void) {
         (void)hipSetDevice(r->device);
         destroy_run(r);
     }
+    drop_grid_pool();
     if (have_cur) (void)hipSetDevice(cur);
     (void)hipGetLastError();
     return rc;
@@ -1387,8 +1479,10 @@ int pt_release(void* h) {
     if (!take_handle(h, &magic)) return fail(PT_ERR_BAD_HANDLE, "not a live handle (released twice?)");
     if (magic == kGridMagic) {
         pt_grid* g = static_cast<pt_grid*>(h);
-        (void)hipDeviceSynchronize();  // no run may still read it
-        free_grid(g);
+        // no run may still read it; memory whose device reports a fault is not kept
+        const bool idle = hipDeviceSynchronize() == hipSuccess;
+        int dev = -1;
+        free_grid(g, idle && hipGetDevice(&dev) == hipSuccess && dev == g->device);
         return PT_OK;
     }
     pt_run* r = static_cast<pt_run*>(h);

@@ -39,3 +39,25 @@ def test_staged_records_begin_above_a_wave_per_simd(pt, precision):
         L.compare_paths(dict(offsets=staged["offsets"][n - 700:] - first, **{k: staged[k][first:] for k in ("cell", "face", "t", "xyz")}),
                         offs, flat, "staged")
         compare(out, r, idx=np.arange(n - 700, n + 1), label="staged", spacing=L.SP)
+
+
+def test_grid_memory_is_reused(pt):
+    """Grids loaded and released in turn take memory that earlier grids of other shapes held; every one
+    gives the oracle's results, whether it was loaded from host or device arrays."""
+    from oracle import oracle as O
+    shapes = [(24, 17, 5), (24, 17, 5), (20, 19, 5), (9, 7, 3), (24, 17, 5), (31, 23, 6), (9, 7, 3)]
+    for q, (nx, ny, nz) in enumerate(shapes):
+        g = C.random_grid(nx, ny, nz, 1.5, 3.0, 500 + q, recharge=1e-3, porosity_field=bool(q % 2))
+        p = C.release(np.random.Generator(np.random.PCG64(70 + q)), 777, nx, ny, nz)
+        r = O.track(g, p)
+        dev = type(g)(**{**vars(g), **{k: torch.from_numpy(np.ascontiguousarray(getattr(g, k))).cuda()
+                                       for k in ("qx", "qy", "qz", "flags", "porosity") if getattr(g, k) is not None}})
+        for kind in (g, dev):
+            for layout in (1, 2):
+                h = pt.pt_load_grid(kind)
+                dp = pt.DeviceParticles.from_numpy(p, "cuda")
+                xyz = torch.empty((p.n, 3), dtype=torch.float64, device="cuda")
+                s = pt.track([h], dp, layout=layout, out_xyz=xyz)
+                h.release()
+                compare(dict(dp.to_numpy(), out_xyz=xyz.cpu().numpy(), summary=s), r, label="grid %d layout %d" % (q, layout),
+                        spacing=(10.0, 10.0, 2.0))
