@@ -130,31 +130,36 @@ __device__ __forceinline__ double adv64_au(double A, double up, double xi, doubl
     return xn;
 }
 
-// The same position by the lean phase, as straight-line code: the result is final when it returns
-// with `ok` unchanged, and has to come from adv64_au when it clears it (|A tau| > 36, or an
-// undecided rounding).  |A tau| < 2^-60 (zero included) has expm1(y)/y = 1; u_p = 0 adds zero.
-__device__ __forceinline__ double adv64_lean(double A, double up, double xi, double tau, bool& ok) {
-    const double y = A * tau;
+// expm1(y) by the lean phase; an undecided rounding goes to the quick phase.  Only |y| <= 36 counts:
+// beyond it the value is not used.
+template <int CR>
+__device__ __forceinline__ double expm1_fast(double y, unsigned& amb) {
     double E;
-    const bool done = ptcr::decided(ptcr::expm1_lean(y), &E);
-    ok = ok & done & (fabs(y) <= 36.0);
+    if (!ptcr::decided(ptcr::expm1_lean(y), &E) && fabs(y) <= 36.0) E = ptcr::expm1_cr<CR>(y, &amb);
+    return E;
+}
+
+// adv64_au from E = expm1(y), y = A tau, |y| <= 36.  |y| < 2^-60 (zero included) has expm1(y)/y = 1;
+// u_p = 0 adds zero.
+__device__ __forceinline__ double adv64_end(double E, double y, double up, double xi, double tau) {
     const double q = ptcr::div_lean(E, y);
     const double psi = (fabs(y) < 0x1p-60) ? 1.0 : q;
     return __builtin_fmin(__builtin_fmax(xi + (up * tau) * psi, 0.0), 1.0);
 }
 
-// All three axes after tau (snapshots, limits).
+// adv64_au with the lean phase, where it is not the step's main cost (snapshots, limits): one general
+// site for undecided roundings and |y| > 36.  The careful pass keeps to the general functions.
 template <int CR>
-__device__ __forceinline__ void adv64_all(const double (&A)[3], const double (&up)[3], const double (&x)[3], double tau,
-                                          double (&out)[3], unsigned& amb) {
-    bool ok = CR == ptcr::CR_FLAG;
+__device__ __forceinline__ double adv64(double A, double up, double xi, double tau, unsigned& amb) {
     if constexpr (CR == ptcr::CR_FLAG) {
-#pragma unroll
-        for (int a = 0; a < 3; ++a) out[a] = adv64_lean(A[a], up[a], x[a], tau, ok);
-    }
-    if (!ok) {
-#pragma unroll
-        for (int a = 0; a < 3; ++a) out[a] = adv64_au<CR>(A[a], up[a], x[a], tau, amb);
+        const double y = A * tau;
+        double E;
+        const bool done = ptcr::decided(ptcr::expm1_lean(y), &E);
+        double xn = adv64_end(E, y, up, xi, tau);
+        if (!((int)done & (int)(fabs(y) <= 36.0))) xn = adv64_au<CR>(A, up, xi, tau, amb);
+        return xn;
+    } else {
+        return adv64_au<CR>(A, up, xi, tau, amb);
     }
 }
 
@@ -243,11 +248,14 @@ __device__ __forceinline__ void estimate_exit64(const double (&u1)[3], const dou
     X.high = X.upw > 0.0;
 }
 
-// Correctly rounded exit time of the chosen axis (exit_time64's operations) by the lean phase, as
-// straight-line code; final when it returns with `ok` unchanged.  The estimates' ranges (u_p in
-// [2^-70, 2^58], D in [2^-50, 1], u_e at least 2^-120 in the ratio form, |x| < 2^128) keep every
-// quotient inside the range of div_by.  |x| < 2^-60 (zero included) has log1p(x)/x = 1.
-__device__ __forceinline__ double exit_time64_lean(const Exit64& X, bool& ok) {
+// Correctly rounded exit time of the chosen axis (exit_time64's operations) with the lean phase, for
+// lanes that come with `ok`.  An undecided rounding is repaired in place where waves are full (5% of
+// wave steps, with half the instructions of the general function), or clears `ok` (REPAIR false).
+// The estimates' ranges (u_p in [2^-70, 2^58], D in [2^-50, 1], u_e at least
+// 2^-120 in the ratio form, |x| < 2^128) keep every quotient inside the range of div_by.
+// |x| < 2^-60 (zero included) has log1p(x)/x = 1.
+template <int CR, bool REPAIR>
+__device__ __forceinline__ double exit_time64_fast(const Exit64& X, bool& ok, unsigned& amb) {
     const double ru = ptcr::recip_lean(X.upw);
     const double r = ptcr::div_by(X.D, X.upw, ru);
     const double x = X.Aw * r;
@@ -259,7 +267,11 @@ __device__ __forceinline__ double exit_time64_lean(const Exit64& X, bool& ok) {
     const double yl = ratio ? 0.0 : sml - (s - big);
     double L;
     const bool done = ptcr::decided(ptcr::log_lean(yh, yl), &L);
-    ok = (int)ok & (int)done;
+    if constexpr (REPAIR) {
+        if (!done && ok) L = ptcr::log_dd_cr<CR>(yh, yl, &amb);
+    } else {
+        ok = (int)ok & (int)done;
+    }
     const double q = ptcr::div_lean(L, ratio ? X.Aw : x);
     double dt = ratio ? q : r * q;
     dt = (fabs(x) < 0x1p-60) ? r : dt;
@@ -569,7 +581,8 @@ __device__ __forceinline__ void eval_snap(const GridDev& G, const typename Real<
     const double tau = s - t;
     double p[3];
     if constexpr (PREC == P64) {
-        adv64_all<CR>(A, up, x, tau, p, amb);
+#pragma unroll
+        for (int a = 0; a < 3; ++a) p[a] = adv64<CR>(A[a], up[a], x[a], tau, amb);
     } else {
 #pragma unroll
         for (int a = 0; a < 3; ++a) p[a] = (double)adv_mix_au(A[a], up[a], x[a], tau);
@@ -1012,9 +1025,10 @@ __device__ __forceinline__ void hash_cell(unsigned long long& h, int32_t c) {
 // FP64: bound by the issue of its VALU instructions when the chip is full, and by their dependent
 // chain when it is not.  So the common path is straight-line: estimates, the record of the next
 // cell (its gather hides behind the arithmetic), one lean exit time, two lean advances; undecided
-// lanes repair their values in branches that most waves skip (about 1 wave step in 60).  1e6
-// particles through a 100x100x10 field: 686 -> 472 VALU instructions per 64 crossings, kernel
-// 2.93 -> 1.94 ms; 4096 particles (one wave per SIMD): 580 -> 330 us.
+// lanes repair their values in branches (an axis' advance in ~6% of the wave steps: small A tau, whose
+// expm1 has few bits to spare).  1e6 particles through a 100x100x10 field: 686 -> 458 VALU instructions
+// per 64 crossings, kernel 2.93 -> 1.84 ms; repairing the logarithm and each expm1 in place, instead
+// of the whole exit time or both advances, took the last 3%.
 template <int PREC, int LAYOUT, int OUT, bool BATCHED, int CR>
 __device__ __forceinline__ int32_t track_step(Lane<PREC>& L, const TrackParams& P, const double* snap,
                                               SnapJob<typename Real<PREC>::T>* job = nullptr) {
@@ -1107,10 +1121,8 @@ __device__ __forceinline__ int32_t track_step(Lane<PREC>& L, const TrackParams& 
     }
 
     if constexpr (kLean) {
-        bool ok = true;
-        const double d = exit_time64_lean(ex, ok);
+        const double d = exit_time64_fast<CR, true>(ex, ex.sure, L.amb);
         dt = ex.sure ? d : dt;
-        if (ex.sure && !ok) dt = exit_core64<CR>(ex.Aw, ex.upw, ex.D, ex.ue, L.amb);
     }
 
     // time limit: t_max, or the end of the current time step when that comes first (transient
@@ -1150,16 +1162,22 @@ __device__ __forceinline__ int32_t track_step(Lane<PREC>& L, const TrackParams& 
     const R Ay = c2 ? A[1] : A[2], uy = c2 ? up[1] : up[2];
     const X xa = c0 ? L.x[1] : L.x[0], xb = c2 ? L.x[1] : L.x[2];
     X na, nb;
-    if constexpr (PREC == P64) {
-        bool ok = kLean;
-        if constexpr (kLean) {
-            na = adv64_lean(Ax, ux, xa, tau, ok);
-            nb = adv64_lean(Ay, uy, xb, tau, ok);
+    if constexpr (kLean) {
+        const double ya = Ax * tau, yb = Ay * tau;
+        const double Ea = expm1_fast<CR>(ya, L.amb), Eb = expm1_fast<CR>(yb, L.amb);
+        na = adv64_end(Ea, ya, ux, xa, tau);
+        nb = adv64_end(Eb, yb, uy, xb, tau);
+        if (!(__builtin_fmax(__builtin_fabs(ya), __builtin_fabs(yb)) <= 36.0)) {
+#pragma unroll 1
+            for (int q = 0; q < 2; ++q) {
+                const double n = adv64_au<CR>(q ? Ay : Ax, q ? uy : ux, q ? xb : xa, tau, L.amb);
+                na = q ? na : n;
+                nb = q ? n : nb;
+            }
         }
-        if (!ok) {
-            na = adv64_au<CR>(Ax, ux, xa, tau, L.amb);
-            nb = adv64_au<CR>(Ay, uy, xb, tau, L.amb);
-        }
+    } else if constexpr (PREC == P64) {
+        na = adv64_au<CR>(Ax, ux, xa, tau, L.amb);
+        nb = adv64_au<CR>(Ay, uy, xb, tau, L.amb);
     } else {
         na = adv_mix_au(Ax, ux, xa, tau);
         nb = adv_mix_au(Ay, uy, xb, tau);
@@ -1169,9 +1187,7 @@ __device__ __forceinline__ int32_t track_step(Lane<PREC>& L, const TrackParams& 
         const X xc = c0 ? L.x[0] : (c1 ? L.x[1] : L.x[2]);
         X ne;
         if constexpr (PREC == P64) {
-            bool ok = kLean;
-            if constexpr (kLean) ne = adv64_lean(Ae, ue, xc, tau, ok);
-            if (!ok) ne = adv64_au<CR>(Ae, ue, xc, tau, L.amb);
+            ne = adv64<CR>(Ae, ue, xc, tau, L.amb);
         } else {
             ne = adv_mix_au(Ae, ue, xc, tau);
         }
@@ -1584,11 +1600,11 @@ __global__ void __launch_bounds__(kBlock) k_track_axes(TrackParams P) {
             ex.ue = pos ? u2 : u1;
             ex.D = (pos ? 1.0 : 0.0) - x;
             const bool feasible = ((int)pos & (int)out2) | ((int)neg & (int)out1);
-            // the ranges of exit_time64_lean's quotients
+            // the ranges of exit_time64_fast's quotients
             const double low = __builtin_fmin(__builtin_fmin(__builtin_fabs(ex.D), __builtin_fabs(ex.upw)), __builtin_fabs(ex.ue));
             const double high = __builtin_fmax(__builtin_fabs(ex.upw), __builtin_fabs(ex.Aw));
             bool ok = (int)(low >= 0x1p-100) & (int)(high <= 0x1p100);
-            double dt = exit_time64_lean(ex, ok);
+            double dt = exit_time64_fast<CR, false>(ex, ok, L.amb);
             if (feasible && !ok) dt = exit_core64<CR>(ex.Aw, ex.upw, ex.D, ex.ue, L.amb);
             dt = feasible ? dt : dinf();
             // the earliest axis, ties to the lowest: face 2 axis + high of the smallest key
@@ -1622,10 +1638,7 @@ __global__ void __launch_bounds__(kBlock) k_track_axes(TrackParams P) {
             }
             // own coordinate after s, and its global value
             auto place = [&](double s) {
-                bool good = true;
-                double xn = adv64_lean(ex.Aw, ex.upw, x, s, good);
-                if (!good) xn = adv64_au<CR>(ex.Aw, ex.upw, x, s, L.amb);
-                return xn;
+                return adv64<CR>(ex.Aw, ex.upw, x, s, L.amb);
             };
             auto world = [&](double xl) {
                 const double o = own == 0 ? G.x0 : (own == 1 ? G.y0 : G.z0), d = own == 0 ? G.dx : (own == 1 ? G.dy : G.dz);
