@@ -3,7 +3,7 @@
 
 One step = one pass of the whole tracking path over one batch: restore the
 released particle state (device-to-device copy), track every particle to its
-stopping condition through the C ABI (pt_track: counter reset, ordering sort,
+stopping condition through the C ABI (pt_track: ordering sort,
 tracking kernel), and read the run summary (pt_results).  Grids and particles
 are resident in HBM before the timed region starts.  The K timed steps are
 enqueued back to back on one stream and their summaries read afterwards, so
@@ -163,7 +163,7 @@ class Case:
         cross = summ[0]["crossings"]
         assert all(s["crossings"] == cross for s in summ), "crossing count changed between steps"
         # the tracking kernel's own device time (events just around its launch), and that of the
-        # whole pt_track sequence (counter reset, ordering sort, tracking kernel, careful pass)
+        # whole pt_track sequence (ordering sort, tracking kernel, careful pass)
         kms = float(np.mean([s["track_ms"] for s in summ]))
         cms = float(np.mean([s["kernel_ms"] for s in summ]))
         return dict(wall_s=wall, ms_per_step=1e3 * wall / steps, crossings_per_step=cross,

@@ -298,7 +298,7 @@ typedef struct {
                                    * their first results and count in cr_ambiguous.              */
     double track_ms;              /* device time of the tracking kernel alone (events recorded   *
                                    * just before and after its launch; kernel_ms also encloses   *
-                                   * the counter reset, the ordering sort and the careful pass)  */
+                                   * the ordering sort and the careful pass)                     */
 } pt_summary;
 
 /* Wait for the run, then fill *out.  Reports asynchronous device errors of
