@@ -1,0 +1,79 @@
+"""Infinite face velocities.
+
+A flow field is checked for finite flows, but flow over pore volume can still overflow: the velocity of
+a face is then infinite, and the method's formulas give NaN (inf - inf, inf * 0).  What the formulas give
+is the result: a NaN coordinate stays NaN.  The oracle evaluates the formulas as they are written, so every kernel form must agree with it, NaN for NaN.
+"""
+import numpy as np
+import pytest
+
+from oracle import oracle as O
+
+from . import helpers as H
+from . import test_gpu_pathline as L
+from .gpu_util import compare, gpu_track, require_gpu
+
+pytestmark = pytest.mark.gpu
+
+# one lane per axis (the library's own launch), static, persistent, face arrays, a captured launch
+FORMS = [dict(), dict(schedule=1, layout=2), dict(schedule=2, layout=2), dict(schedule=1, layout=1), dict(use_graph=1)]
+SNAPS = np.array([0.0, 0.3, 0.75, 1.0, 2.5, 7.0])
+VOL = 1e-300     # dx dy dz of the cells below: a flow of 1e-300 is a velocity of 1, one above 2e8 is infinite
+
+
+@pytest.fixture(scope="module")
+def pt():
+    return require_gpu()
+
+
+def _grid(nx, ny, nz):
+    return H.box_grid(nx, ny, nz, 1e-100, 1e-100, 1e-100, porosity=1.0)
+
+
+def _check(g, p, label, **kw):
+    r = O.track(g, p, **kw)
+    rs = O.track(g, p, snap_times=SNAPS, **kw)
+    for f in FORMS:
+        out = gpu_track([g], p, **f, **kw)
+        compare(out, r, label="%s %s" % (label, f))
+        assert out["summary"]["crossings"] == int(r.ncross.sum()), label
+        compare(gpu_track([g], p, snap_times=SNAPS, **f, **kw), rs, label="%s %s, snapshots" % (label, f))
+    return r
+
+
+@pytest.mark.parametrize("axis", [0, 1, 2])
+@pytest.mark.parametrize("t_max", [np.inf, 2.25])
+def test_nan_coordinates_stay_nan(pt, axis, t_max):
+    """The first of three cells along an axis has infinite velocities of one sign on another one: the
+    particle's coordinate there is NaN from the first step on, also in the cells after it, whose velocities
+    are finite."""
+    shape = [1, 1, 1]
+    shape[axis] = 3
+    g = _grid(*shape)
+    q = [g.qx, g.qy, g.qz]
+    other = (axis + 1) % 3
+    q[axis][:] = VOL
+    q[other][:] = 0.01 * VOL
+    first = [slice(None)] * 3
+    first[2 - axis] = 0
+    q[other][tuple(first)] = 1e10
+    loc = [[0.25, 0.5, 0.0], [0.5, 0.5, 1.0], [0.125, 0.0, 0.5], [1.0, 0.75, 0.25]]
+    xs = [np.roll(v, axis) for v in loc]
+    p = H.particles([0] * len(xs), *np.array(xs).T)
+    r = _check(g, p, "axis %d" % axis, t_max=t_max, max_steps=50)
+    assert np.isnan(getattr(r, ("xi", "eta", "zeta")[other])).all()
+    assert r.ncross.min() == (3 if np.isinf(t_max) else 2)
+
+
+def test_pathline_records_keep_nan(pt):
+    g = _grid(3, 1, 1)
+    g.qx[:] = VOL
+    g.qy[:] = 0.01 * VOL
+    g.qy[:, :, 0] = 1e10
+    p = H.particles([0, 0], [0.25, 0.5], [0.5, 0.5], [0.5, 0.0])
+    _, offs, flat = L.oracle_paths(g, p)
+    for f in FORMS[:3]:
+        _, paths = L.gpu_pathlines(pt, [g], p, **f)
+        assert np.array_equal(paths["offsets"], offs)
+        for k in ("t", "xyz", "cell", "face"):
+            assert np.array_equal(paths[k], flat[k], equal_nan=paths[k].dtype.kind == "f"), (f, k)
