@@ -1682,7 +1682,10 @@ __global__ void __launch_bounds__(kBlock) k_track_axes(TrackParams P) {
             const double high = __builtin_fmax(__builtin_fabs(ex.upw), __builtin_fabs(ex.Aw));
             bool ok = (int)(low >= 0x1p-100) & (int)(high <= 0x1p100);
             double dt = exit_time64_fast<CR, false>(ex, ok, L.amb);
-            if (feasible && !ok) dt = exit_core64<CR>(ex.Aw, ex.upw, ex.D, ex.ue, L.amb);
+            if (feasible && !ok) {
+                dt = exit_core64<CR>(ex.Aw, ex.upw, ex.D, ex.ue, L.amb);
+                dt = dt < dinf() ? dt : dinf();   // a time that is NaN is never the earliest
+            }
             dt = feasible ? dt : dinf();
             // the earliest axis, ties to the lowest: face 2 axis + high of the smallest key
             const double d1 = dpp<kNext>(dt), d2 = dpp<kOther>(dt);

@@ -2,7 +2,8 @@
 
 A flow field is checked for finite flows, but flow over pore volume can still overflow: the velocity of
 a face is then infinite, and the method's formulas give NaN (inf - inf, inf * 0).  What the formulas give
-is the result: a NaN coordinate stays NaN.  The oracle evaluates the formulas as they are written, so every kernel form must agree with it, NaN for NaN.
+is the result: a NaN coordinate stays NaN, and an exit time that is NaN is never the earliest.  The
+oracle evaluates the formulas as they are written, so every kernel form must agree with it, NaN for NaN.
 """
 import numpy as np
 import pytest
@@ -63,6 +64,21 @@ def test_nan_coordinates_stay_nan(pt, axis, t_max):
     r = _check(g, p, "axis %d" % axis, t_max=t_max, max_steps=50)
     assert np.isnan(getattr(r, ("xi", "eta", "zeta")[other])).all()
     assert r.ncross.min() == (3 if np.isinf(t_max) else 2)
+
+
+@pytest.mark.parametrize("t_max", [np.inf, 1.5])
+def test_no_face_is_reached_in_nan_time(pt, t_max):
+    """Velocities that grow to infinity along every axis: each exit time is NaN, so no face is reachable
+    and the particle strands -- at the time limit when there is one -- without a crossing."""
+    g = _grid(2, 2, 2)
+    for q, a in ((g.qx, 2), (g.qy, 1), (g.qz, 0)):
+        q[:] = VOL
+        hi = [slice(None)] * 3
+        hi[a] = slice(1, None)
+        q[tuple(hi)] = 1e10
+    p = H.particles([0, 0, 0], [0.5, 0.25, 0.75], [0.5, 0.125, 0.5], [0.5, 1.0, 0.25])
+    r = _check(g, p, "nan exits", t_max=t_max, max_steps=50)
+    assert (r.ncross == 0).all() and (r.status == 5).all()
 
 
 def test_pathline_records_keep_nan(pt):
