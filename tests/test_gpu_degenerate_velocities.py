@@ -1,9 +1,10 @@
-"""Infinite face velocities.
+"""Infinite face velocities and negative zeros.
 
 A flow field is checked for finite flows, but flow over pore volume can still overflow: the velocity of
 a face is then infinite, and the method's formulas give NaN (inf - inf, inf * 0).  What the formulas give
 is the result: a NaN coordinate stays NaN, and an exit time that is NaN is never the earliest.  The
 oracle evaluates the formulas as they are written, so every kernel form must agree with it, NaN for NaN.
+The same holds for the sign of a zero coordinate.
 """
 import numpy as np
 import pytest
@@ -31,6 +32,10 @@ def _grid(nx, ny, nz):
     return H.box_grid(nx, ny, nz, 1e-100, 1e-100, 1e-100, porosity=1.0)
 
 
+def _same_sign(a, b):
+    return np.array_equal(np.signbit(a) | np.isnan(a), np.signbit(b) | np.isnan(b))
+
+
 def _check(g, p, label, **kw):
     r = O.track(g, p, **kw)
     rs = O.track(g, p, snap_times=SNAPS, **kw)
@@ -38,6 +43,8 @@ def _check(g, p, label, **kw):
         out = gpu_track([g], p, **f, **kw)
         compare(out, r, label="%s %s" % (label, f))
         assert out["summary"]["crossings"] == int(r.ncross.sum()), label
+        for k in ("xi", "eta", "zeta"):
+            assert _same_sign(out[k], getattr(r, k)), (label, f, k)
         compare(gpu_track([g], p, snap_times=SNAPS, **f, **kw), rs, label="%s %s, snapshots" % (label, f))
     return r
 
@@ -79,6 +86,22 @@ def test_no_face_is_reached_in_nan_time(pt, t_max):
     p = H.particles([0, 0, 0], [0.5, 0.25, 0.75], [0.5, 0.125, 0.5], [0.5, 1.0, 0.25])
     r = _check(g, p, "nan exits", t_max=t_max, max_steps=50)
     assert (r.ncross == 0).all() and (r.status == 5).all()
+
+
+def test_negative_zero_coordinates(pt):
+    """A coordinate of -0.0 on an axis without motion keeps its sign, one that moves becomes what the sum
+    gives; on the exit axis it is the face."""
+    g = H.box_grid(4, 2, 2, 1.0, 1.0, 1.0, porosity=1.0)
+    g.qx[:] = 1.0
+    g.qy[:, :, 2:] = 1e-3
+    nz = -0.0
+    p = H.particles([0, 0, 0, 1, 0], [nz, 0.5, 0.25, nz, nz], [nz, nz, 0.5, nz, 0.0], [nz, 0.0, nz, 0.5, nz])
+    for kw in (dict(), dict(t_max=0.5), dict(t_max=1.25), dict(direction=-1, t_max=3.0), dict(max_steps=1)):
+        r = _check(g, p, "negative zero %s" % kw, **kw)
+    assert np.signbit(r.zeta[0])
+    g.qx[:] = 0.0
+    g.qy[:] = 0.0
+    _check(g, p, "negative zero, no flow", t_max=1.0)
 
 
 def test_pathline_records_keep_nan(pt):
