@@ -131,11 +131,16 @@ __device__ __forceinline__ double adv64_au(double A, double up, double xi, doubl
 }
 
 // expm1(y) by the lean phase; an undecided rounding goes to the quick phase.  Only |y| <= 36 counts:
-// beyond it the value is not used.
+// beyond it the value is not used, and on an axis at rest (u_p = 0) neither, so that what the accurate
+// phase leaves undecided there is no reason to track the particle again.
 template <int CR>
-__device__ __forceinline__ double expm1_fast(double y, unsigned& amb) {
+__device__ __forceinline__ double expm1_fast(double y, double up, unsigned& amb) {
     double E;
-    if (!ptcr::decided(ptcr::expm1_lean(y), &E) && fabs(y) <= 36.0) E = ptcr::expm1_cr<CR>(y, &amb);
+    if (!ptcr::decided(ptcr::expm1_lean(y), &E) && fabs(y) <= 36.0) {
+        unsigned undecided = 0u;
+        E = ptcr::expm1_cr<CR>(y, &undecided);
+        if (up != 0.0) amb += undecided;
+    }
     return E;
 }
 
@@ -1243,7 +1248,7 @@ __device__ __forceinline__ int32_t track_step(Lane<PREC>& L, const TrackParams& 
     X na, nb;
     if constexpr (kLean) {
         const double ya = Ax * tau, yb = Ay * tau;
-        const double Ea = expm1_fast<CR>(ya, L.amb), Eb = expm1_fast<CR>(yb, L.amb);
+        const double Ea = expm1_fast<CR>(ya, ux, L.amb), Eb = expm1_fast<CR>(yb, uy, L.amb);
         na = adv64_end(Ea, ya, ux, xa, tau);
         nb = adv64_end(Eb, yb, uy, xb, tau);
         if (!((int)(__builtin_fabs(ya) <= 36.0) & (int)(__builtin_fabs(yb) <= 36.0) & (int)plain(xa, xb))) {

@@ -1,10 +1,11 @@
-"""Infinite face velocities and negative zeros.
+"""Infinite face velocities, negative zeros and undecided roundings that a track does not need.
 
 A flow field is checked for finite flows, but flow over pore volume can still overflow: the velocity of
 a face is then infinite, and the method's formulas give NaN (inf - inf, inf * 0).  What the formulas give
 is the result: a NaN coordinate stays NaN, and an exit time that is NaN is never the earliest.  The
 oracle evaluates the formulas as they are written, so every kernel form must agree with it, NaN for NaN.
-The same holds for the sign of a zero coordinate.
+The same holds for the sign of a zero coordinate, and for what counts as a recheck: an evaluation whose
+value the track does not use hands no particle to the careful pass.
 """
 import numpy as np
 import pytest
@@ -102,6 +103,50 @@ def test_negative_zero_coordinates(pt):
     g.qx[:] = 0.0
     g.qy[:] = 0.0
     _check(g, p, "negative zero, no flow", t_max=1.0)
+
+
+def _unit(q):
+    """One cell of unit pore volume: face flows are velocities."""
+    g = H.box_grid(1, 1, 1, 1.0, 1.0, 1.0, porosity=1.0)
+    for a, (lo, hi) in zip((g.qx, g.qy, g.qz), q):
+        a.reshape(-1)[:] = lo, hi
+    return g
+
+
+# velocities whose exp or log argument lies within 2^-96 of a rounding boundary (found by search)
+UNDECIDED_EXIT = float.fromhex("0x1.0000000000006p+0")   # log1p(u2 - 1)
+UNUSED = {
+    # no motion on x (u_p = 0), whose expm1(2^-52 * 1) is undecided; the limit comes first
+    "axis at rest": (_unit([(-2.0 ** -53, 2.0 ** -53), (0.25, 0.25), (0.0, 0.0)]), (0.5, 0.25, 0.5), dict(t_max=1.0)),
+}
+
+
+@pytest.mark.parametrize("case", sorted(UNUSED))
+def test_unused_evaluations_hand_nothing_over(pt, case):
+    g, loc, kw = UNUSED[case]
+    p = H.particles([0] * 3, *[[v] * 3 for v in loc])
+    r = O.track(g, p, **kw)
+    for f in FORMS:
+        out = gpu_track([g], p, **f, **kw)
+        compare(out, r, label="%s %s" % (case, f))
+        assert out["summary"]["recheck_tracks"] == 0, (case, f, out["summary"]["recheck_tracks"])
+
+
+@pytest.mark.parametrize("q, loc, kw", [
+    ([(1.0, UNDECIDED_EXIT), (0.0, 0.0), (0.0, 0.0)], (0.0, 0.5, 0.5), dict()),                        # the exit time taken
+    ([(1.0, UNDECIDED_EXIT), (1.0, UNDECIDED_EXIT), (0.0, 0.0)], (0.0, 0.0, 0.5), dict()),             # a tie
+    ([(0.5, 0.5 + 2.0 ** -52), (0.25, 0.25), (0.0, 0.0)], (0.0, 0.25, 0.5), dict(t_max=1.0)),         # an advance to the limit
+    ([(0.5, 0.5 + 2.0 ** -52), (1.0, 1.0), (0.0, 0.0)], (0.0, 0.0, 0.5), dict()),                      # another axis' advance
+], ids=["exit time", "tie", "limit", "advance"])
+def test_used_evaluations_are_handed_over(pt, q, loc, kw):
+    """The other side: an undecided value that the track uses reaches the careful pass in every form."""
+    g = _unit(q)
+    p = H.particles([0] * 3, *[[v] * 3 for v in loc])
+    r = O.track(g, p, **kw)
+    for f in FORMS:
+        out = gpu_track([g], p, **f, **kw)
+        compare(out, r, label=str(f))
+        assert out["summary"]["recheck_tracks"] == 3, f
 
 
 def test_pathline_records_keep_nan(pt):
