@@ -115,9 +115,16 @@ def _unit(q):
 
 # velocities whose exp or log argument lies within 2^-96 of a rounding boundary (found by search)
 UNDECIDED_EXIT = float.fromhex("0x1.0000000000006p+0")   # log1p(u2 - 1)
+# expm1((u2 - u1) dt), dt the exit time from 0.75
+UNDECIDED_ADVANCE = (float.fromhex("0x1.8000000000002p+1"), float.fromhex("0x1.7ffffffffffffp+1"))
 UNUSED = {
     # no motion on x (u_p = 0), whose expm1(2^-52 * 1) is undecided; the limit comes first
     "axis at rest": (_unit([(-2.0 ** -53, 2.0 ** -53), (0.25, 0.25), (0.0, 0.0)]), (0.5, 0.25, 0.5), dict(t_max=1.0)),
+    # leaves through x, where its coordinate is the face's whatever the advance to it would give
+    "exit axis": (_unit([UNDECIDED_ADVANCE, (0.0, 0.0), (0.0, 0.0)]), (0.75, 0.5, 0.5), dict()),
+    "exit axis, beside others": (_unit([(0.1, 0.1), UNDECIDED_ADVANCE, (0.1, 0.1)]), (0.0, 0.75, 0.5), dict()),
+    # leaves through x four times sooner than through y, whose exit time is undecided
+    "far axis": (_unit([(4.0, 4.0), (1.0, UNDECIDED_EXIT), (0.0, 0.0)]), (0.0, 0.0, 0.5), dict()),
 }
 
 
