@@ -1259,9 +1259,14 @@ int pt_track(const pt_grid* const* grids, int32_t n_grids, const pt_particles* p
     // a graph always resets: its launches do not depend on the run's history
     build_seq(PL, p->n, o->use_graph || !r->cleared, &RP, &P, &SP, &SC, seq);
     r->tracks = seq.track_at >= 0;
+    // Whether the launches run now.  Of the default stream the runtime does not say so while a blocking
+    // stream is being captured; the call goes on, and the counters are taken as not cleared by it.
     hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-    hipError_t e = hipStreamIsCapturing(s, &cap);
-    if (e == hipSuccess) e = hipEventRecord(r->ev0, s);
+    if (hipStreamIsCapturing(s, &cap) != hipSuccess) {
+        (void)hipGetLastError();
+        cap = hipStreamCaptureStatusInvalidated;
+    }
+    hipError_t e = hipEventRecord(r->ev0, s);
     if (e == hipSuccess) {
         if (o->use_graph) {
             // key: every launch's function, shape, dynamic LDS and argument bytes

@@ -1,0 +1,31 @@
+"""libpt's host code over a HIP runtime that runs no kernels (CPU).
+
+tests/native/fake_hip.c defines the HIP calls the library makes and is linked before the runtime, so the
+library's allocations, releases and launches are seen and limited from outside: here calls
+whose stream the runtime refuses to describe.
+"""
+import os
+import subprocess
+
+import pytest
+
+from paper_2302_13590_amd import pt
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+ROOT = os.path.dirname(HERE)
+
+
+@pytest.fixture(scope="module")
+def exe(tmp_path_factory):
+    out = str(tmp_path_factory.mktemp("fake_hip") / "fake_hip")
+    lib = os.path.dirname(pt.LIB_PATH)
+    subprocess.check_call(["gcc", "-std=c99", "-O1", "-g", "-Wall", "-rdynamic", "-I", os.path.join(ROOT, "include"), "-o", out,
+                           os.path.join(HERE, "native", "fake_hip.c"), pt.LIB_PATH, "-Wl,-rpath," + lib,
+                           "-Wl,--allow-shlib-undefined"])
+    return out
+
+
+@pytest.mark.parametrize("scenario", ["capture_refused"])
+def test_host_runtime(exe, scenario):
+    r = subprocess.run([exe, scenario], capture_output=True, text=True, timeout=120)
+    assert r.returncode == 0 and r.stdout.strip() == "ok", r.stdout[-2000:] + r.stderr[-2000:]
