@@ -152,6 +152,42 @@ struct pt_run {
 
 namespace {
 
+// Device memory of released grids, kept for the next load of about its size on the same device: a
+// loop over realisations then neither maps nor unmaps memory (1e5 cells from host arrays: load 265 ->
+// 180 us, release 96 -> 29 us, with one block for all arrays of a grid instead of eight).  At most
+// kGridPoolMax blocks and kGridPoolBytes; guarded by g_mu; a block enters only after its device has been
+// synchronised.  Any device allocation of the library that finds no memory gives the pool back and tries
+// again, and pt_shutdown frees it.
+struct GridBlock {
+    void* mem;
+    size_t bytes;
+    int device;
+};
+std::vector<GridBlock> g_grid_pool;
+constexpr size_t kGridPoolMax = 8;
+constexpr size_t kGridPoolBytes = (size_t)256 << 20;
+
+void drop_grid_pool() {
+    std::vector<GridBlock> v;
+    {
+        std::lock_guard<std::mutex> lk(g_mu);
+        v.swap(g_grid_pool);
+    }
+    for (const GridBlock& b : v) (void)hipFree(b.mem);
+}
+
+// Device memory for a grid or a run.
+template <class T>
+hipError_t device_alloc(T** p, size_t bytes) {
+    hipError_t e = hipMalloc(p, bytes);
+    if (e == hipErrorOutOfMemory) {
+        (void)hipGetLastError();
+        drop_grid_pool();
+        e = hipMalloc(p, bytes);
+    }
+    return e;
+}
+
 std::vector<pt_run*> g_pool;  // released runs kept for reuse (guarded by g_mu)
 // Released runs kept: enough for a few dozen calls in flight on one stream (each keeps its
 // cached graph, events, counters and ordering buffers); pt_shutdown frees them.
@@ -189,7 +225,7 @@ int new_run(int device, pt_run** out) {
     pt_run* r = new pt_run();
     r->magic = kRunMagic;
     r->device = device;
-    hipError_t e = hipMalloc(&r->d_counters, sizeof(Counters));
+    hipError_t e = device_alloc(&r->d_counters, sizeof(Counters));
     if (e == hipSuccess) e = hipHostMalloc(&r->h_counters, sizeof(Counters), hipHostMallocCoherent);
     if (e == hipSuccess) e = hipEventCreate(&r->ev0);
     if (e == hipSuccess) e = hipEventCreate(&r->ev1);
@@ -217,7 +253,7 @@ int ensure_tables(pt_run* r, size_t bytes) {
         r->graph = nullptr;
         r->graph_key.clear();
     }
-    HIP_TRY(hipMalloc(&r->d_tables, bytes));
+    HIP_TRY(device_alloc(&r->d_tables, bytes));
     HIP_TRY(hipHostMalloc(&r->h_tables, bytes, hipHostMallocDefault));
     r->d_tables_bytes = r->h_tables_bytes = bytes;
     return PT_OK;
@@ -230,7 +266,7 @@ int ensure_sort(pt_run* r, size_t bytes) {
     if (r->d_sort) (void)hipFree(r->d_sort);
     r->d_sort = nullptr;
     r->d_sort_bytes = 0;
-    HIP_TRY(hipMalloc(&r->d_sort, bytes));
+    HIP_TRY(device_alloc(&r->d_sort, bytes));
     r->d_sort_bytes = bytes;
     return PT_OK;
 }
@@ -240,7 +276,7 @@ int ensure_recheck(pt_run* r, size_t bytes) {
     if (r->d_recheck) (void)hipFree(r->d_recheck);
     r->d_recheck = nullptr;
     r->d_recheck_bytes = 0;
-    HIP_TRY(hipMalloc(&r->d_recheck, bytes));
+    HIP_TRY(device_alloc(&r->d_recheck, bytes));
     r->d_recheck_bytes = bytes;
     return PT_OK;
 }
@@ -250,7 +286,7 @@ int ensure_scan(pt_run* r, size_t bytes) {
     if (r->d_scan) (void)hipFree(r->d_scan);
     r->d_scan = nullptr;
     r->d_scan_bytes = 0;
-    HIP_TRY(hipMalloc(&r->d_scan, bytes));
+    HIP_TRY(device_alloc(&r->d_scan, bytes));
     r->d_scan_bytes = bytes;
     return PT_OK;
 }
@@ -326,29 +362,6 @@ int check_host_grid(const pt_grid_desc* d) {
     return PT_OK;
 }
 
-// Device memory of released grids, kept for the next load of about its size on the same device: a
-// loop over realisations then neither maps nor unmaps memory (1e5 cells from host arrays: load 265 ->
-// 180 us, release 96 -> 29 us, with one block for all arrays of a grid instead of eight).  At most kGridPoolMax blocks and kGridPoolBytes; guarded by g_mu; a block
-// enters only after its device has been synchronised; an allocation that fails empties the pool and
-// tries again, and pt_shutdown frees it.
-struct GridBlock {
-    void* mem;
-    size_t bytes;
-    int device;
-};
-std::vector<GridBlock> g_grid_pool;
-constexpr size_t kGridPoolMax = 8;
-constexpr size_t kGridPoolBytes = (size_t)256 << 20;
-
-void drop_grid_pool() {
-    std::vector<GridBlock> v;
-    {
-        std::lock_guard<std::mutex> lk(g_mu);
-        v.swap(g_grid_pool);
-    }
-    for (const GridBlock& b : v) (void)hipFree(b.mem);
-}
-
 hipError_t grid_memory(pt_grid* g, size_t bytes) {
     {
         std::lock_guard<std::mutex> lk(g_mu);
@@ -362,12 +375,7 @@ hipError_t grid_memory(pt_grid* g, size_t bytes) {
             }
         }
     }
-    hipError_t e = hipMalloc(&g->mem, bytes);
-    if (e == hipErrorOutOfMemory) {
-        (void)hipGetLastError();
-        drop_grid_pool();
-        e = hipMalloc(&g->mem, bytes);
-    }
+    const hipError_t e = device_alloc(&g->mem, bytes);
     g->bytes = e == hipSuccess ? bytes : 0;
     return e;
 }

@@ -115,6 +115,15 @@ static pt_grid* load(int nx) {
     CHECK(rc == PT_OK, "load of %d cells: %d (%s)", nx, rc, pt_last_error());
     return g;
 }
+static size_t bytes_of(int nx) {   /* device memory of such a grid */
+    size_t before = live[device];
+    pt_grid* g = load(nx);
+    size_t b = live[device] - before;
+    pt_release(g);
+    pt_shutdown();
+    return b;
+}
+
 enum { PLAIN, SORTED, SERIES, COUNT, KINDS };   /* calls with different buffers */
 static int track(pt_grid* g, int kind, int64_t n) {
     static char somewhere[8];
@@ -152,6 +161,58 @@ static int track(pt_grid* g, int kind, int64_t n) {
 
 /* ---- scenarios ---------------------------------------------------------------------------- */
 
+/* A call whose run buffers fit only in the memory of a grid that was released before it; the sizes of
+ * that grid let every allocation of the call be the first without memory. */
+static void run_buffers(void) {
+    for (int kind = 0; kind < KINDS; ++kind) {
+        const int64_t n = 1 << 20;
+        pt_grid* a = load(1000);
+        const size_t grid = live[0];
+        CHECK(track(a, kind, n) == PT_OK, "kind %d without a limit: %s", kind, pt_last_error());
+        const size_t run = live[0] - grid;
+        pt_release(a);
+        pt_shutdown();
+        for (int nx = 2100; nx < 400000; nx = nx * 3 / 2) {
+            a = load(1000);
+            pt_release(load(nx));
+            limit[0] = live[0] > grid + run ? live[0] : grid + run;   /* no room for anything else */
+            CHECK(track(a, kind, n) == PT_OK, "kind %d beside a released grid of %d: %s", kind, nx, pt_last_error());
+            CHECK(live[0] == grid + run, "kind %d beside a released grid of %d: %zu bytes live, %zu used", kind, nx, live[0], grid + run);
+            limit[0] = (size_t)1 << 40;
+            pt_release(a);
+            pt_shutdown();
+        }
+    }
+    /* an allocation that does not fit at all is refused, and the next call runs */
+    pt_grid* a = load(1000);
+    pt_release(load(3000));
+    limit[0] = live[0] + 1024;
+    CHECK(track(a, SORTED, 1 << 20) == PT_ERR_OOM, "refusal");
+    CHECK(nlive[0] <= 2, "%d blocks kept after a refusal", nlive[0]);
+    limit[0] = (size_t)1 << 40;
+    CHECK(track(a, SORTED, 1 << 20) == PT_OK, "after a refusal: %s", pt_last_error());
+    pt_release(a);
+}
+
+/* A grid's memory is taken again by a load of about its size, and by that only. */
+static void reuse(void) {
+    const size_t b = bytes_of(1000);
+    pt_grid* g = load(1000);
+    pt_release(g);
+    int m = mallocs, f = frees;
+    for (int q = 0; q < 20; ++q) pt_release(load(1000 - q));
+    CHECK(mallocs == m && frees == f, "%d allocations and %d frees in a loop over one size", mallocs - m, frees - f);
+    CHECK(live[0] == b, "%zu bytes live, one grid takes %zu", live[0], b);
+    g = load(400);   /* less than half */
+    CHECK(mallocs == m + 1, "a block of more than twice the size was taken");
+    pt_grid* h = load(1100);
+    CHECK(mallocs == m + 2, "a block too small was taken");
+    pt_release(g);
+    pt_release(h);
+    pt_shutdown();
+    CHECK(live[0] == 0 && nlive[0] == 0, "%zu bytes live after the shutdown", live[0]);
+}
+
 /* The default stream while another stream is being captured: the runtime refuses to say whether it is
  * being captured.  The call runs, and does not rely on what an uncertain call left behind. */
 static void capture_refused(void) {
@@ -174,7 +235,9 @@ static void capture_refused(void) {
 
 int main(int argc, char** argv) {
     const char* s = argc > 1 ? argv[1] : "";
-    if (!strcmp(s, "capture_refused")) capture_refused();
+    if (!strcmp(s, "run_buffers")) run_buffers();
+    else if (!strcmp(s, "reuse")) reuse();
+    else if (!strcmp(s, "capture_refused")) capture_refused();
     else return 2;
     pt_shutdown();
     if (live[0] || live[1]) {
