@@ -306,7 +306,11 @@ typedef struct {
 int pt_results(pt_run* run, pt_summary* out);
 
 /* Release a pt_grid* or pt_run* (waits for a run still in flight).  NULL is a
- * no-op.  A pointer that is not a live handle gives PT_ERR_BAD_HANDLE. */
+ * no-op.  A pointer that is not a live handle gives PT_ERR_BAD_HANDLE.  The
+ * device memory of released grids is kept for later loads: at most 8 blocks
+ * and 256 MiB on each device, the oldest given up first.  An allocation of this
+ * library that finds no memory gives all of it back first; pt_shutdown does
+ * when other users of the device need it. */
 int pt_release(void* handle);
 
 /* ---- allocation-free tracking ----------------------------------------------------------- */
@@ -351,8 +355,8 @@ int pt_track_noalloc(const pt_grid* const* grids, int32_t n_grids, const pt_part
                      const pt_track_opts* o, void* hip_stream, int64_t* counts);
 
 /* Release everything the library holds: every live grid and run handle (waiting for the
- * devices they use first) and the released runs kept for reuse, with their cached hipGraphs,
- * events and device and pinned buffers.  Afterwards every earlier handle is invalid
+ * devices they use first), the released runs kept for reuse, with their cached hipGraphs, events and
+ * device and pinned buffers, and the memory kept of released grids.  Afterwards every earlier handle is invalid
  * (PT_ERR_BAD_HANDLE), and the library can be used again from scratch.  Call it when no other
  * call of this library is in progress, before the HIP runtime is torn down at process exit
  * (the Python binding registers it with atexit), so that no HIP object of the library outlives

@@ -11,6 +11,7 @@
 #include <mutex>
 #include <string>
 #include <unordered_set>
+#include <utility>
 #include <vector>
 
 #include "pt.h"
@@ -118,6 +119,7 @@ struct pt_grid {
     GridDev gd;
     void* mem = nullptr;   // one allocation for all its arrays
     size_t bytes = 0;
+    pt_grid* next = nullptr;   // released grids whose memory is kept: the next younger one
 };
 
 struct pt_run {
@@ -152,28 +154,64 @@ struct pt_run {
 
 namespace {
 
-// Device memory of released grids, kept for the next load of about its size on the same device: a
-// loop over realisations then neither maps nor unmaps memory (1e5 cells from host arrays: load 265 ->
-// 180 us, release 96 -> 29 us, with one block for all arrays of a grid instead of eight).  At most
-// kGridPoolMax blocks and kGridPoolBytes; guarded by g_mu; a block enters only after its device has been
-// synchronised.  Any device allocation of the library that finds no memory gives the pool back and tries
-// again, and pt_shutdown frees it.
-struct GridBlock {
-    void* mem;
-    size_t bytes;
-    int device;
-};
-std::vector<GridBlock> g_grid_pool;
-constexpr size_t kGridPoolMax = 8;
+// Memory of released grids, kept for the next load of about its size on the same device: a loop over
+// realisations then neither maps nor unmaps memory (1e5 cells from host arrays: load 265 -> 180 us, release
+// 96 -> 29 us, with one block for all arrays of a grid instead of eight).  For each device at most
+// kGridPoolMax blocks and kGridPoolBytes; the oldest leave first.  Guarded by g_mu; a block enters only
+// after its device has been synchronised.  Any device allocation of the library that finds no memory gives
+// the blocks back and tries again, and pt_shutdown frees them.  A list through the grids themselves, so
+// that pt_release allocates nothing.
+pt_grid* g_grid_pool = nullptr;   // oldest first
+constexpr int kGridPoolMax = 8;
 constexpr size_t kGridPoolBytes = (size_t)256 << 20;
 
-void drop_grid_pool() {
-    std::vector<GridBlock> v;
+void free_grids(pt_grid* list) {
+    while (list) {
+        pt_grid* g = list;
+        list = g->next;
+        if (g->mem) (void)hipFree(g->mem);
+        delete g;
+    }
+}
+
+// Keep the memory of a grid whose device has no work left on it.
+void keep_grid(pt_grid* g) {
+    if (g->bytes > kGridPoolBytes) return free_grids(g);
+    pt_grid* out = nullptr;
     {
         std::lock_guard<std::mutex> lk(g_mu);
-        v.swap(g_grid_pool);
+        int blocks = 1;
+        size_t bytes = g->bytes;
+        pt_grid** end = &g_grid_pool;
+        for (; *end; end = &(*end)->next) {
+            if ((*end)->device != g->device) continue;
+            ++blocks;
+            bytes += (*end)->bytes;
+        }
+        *end = g;
+        for (pt_grid** q = &g_grid_pool; blocks > kGridPoolMax || bytes > kGridPoolBytes;) {
+            pt_grid* b = *q;
+            if (b->device != g->device) {
+                q = &b->next;
+                continue;
+            }
+            --blocks;
+            bytes -= b->bytes;
+            *q = b->next;
+            b->next = out;
+            out = b;
+        }
     }
-    for (const GridBlock& b : v) (void)hipFree(b.mem);
+    free_grids(out);
+}
+
+void drop_grid_pool() {
+    pt_grid* out = nullptr;
+    {
+        std::lock_guard<std::mutex> lk(g_mu);
+        std::swap(out, g_grid_pool);
+    }
+    free_grids(out);
 }
 
 // Device memory for a grid or a run.
@@ -362,37 +400,27 @@ int check_host_grid(const pt_grid_desc* d) {
     return PT_OK;
 }
 
+// Memory for a grid's arrays: a kept block that is large enough and at most twice that, else a new one.
 hipError_t grid_memory(pt_grid* g, size_t bytes) {
+    pt_grid* kept = nullptr;
     {
         std::lock_guard<std::mutex> lk(g_mu);
-        for (size_t q = 0; q < g_grid_pool.size(); ++q) {
-            const GridBlock& b = g_grid_pool[q];
-            if (b.device == g->device && b.bytes >= bytes && b.bytes <= 2 * bytes) {
-                g->mem = b.mem;
-                g->bytes = b.bytes;
-                g_grid_pool.erase(g_grid_pool.begin() + (ptrdiff_t)q);
-                return hipSuccess;
-            }
+        pt_grid** q = &g_grid_pool;
+        while (*q && !((*q)->device == g->device && (*q)->bytes >= bytes && (*q)->bytes <= 2 * bytes)) q = &(*q)->next;
+        if (*q) {
+            kept = *q;
+            *q = kept->next;
         }
+    }
+    if (kept) {
+        g->mem = kept->mem;
+        g->bytes = kept->bytes;
+        delete kept;
+        return hipSuccess;
     }
     const hipError_t e = device_alloc(&g->mem, bytes);
     g->bytes = e == hipSuccess ? bytes : 0;
     return e;
-}
-
-// Free a grid whose device has no work left on it; `keep`: its memory may go to the pool.
-void free_grid(pt_grid* g, bool keep = false) {
-    if (g->mem && keep) {
-        std::lock_guard<std::mutex> lk(g_mu);
-        size_t held = g->bytes;
-        for (const GridBlock& b : g_grid_pool) held += b.bytes;
-        if (g_grid_pool.size() < kGridPoolMax && held <= kGridPoolBytes) {
-            g_grid_pool.push_back({g->mem, g->bytes, g->device});
-            g->mem = nullptr;
-        }
-    }
-    if (g->mem) (void)hipFree(g->mem);
-    delete g;
 }
 
 // Places arrays in one block, 256-byte aligned: a first walk (base null) sums their sizes.
@@ -1003,7 +1031,7 @@ int pt_load_grid(const pt_grid_desc* d, void* hip_stream, pt_grid** out) {
     hipError_t e = grid_memory(g, m.used);
     if (e != hipSuccess) {
         (void)hipGetLastError();
-        free_grid(g);
+        free_grids(g);
         return fail(hip_code(e), "grid allocation failed: %s", hipGetErrorString(e));
     }
     m.base = static_cast<char*>(g->mem);
@@ -1047,11 +1075,11 @@ int pt_load_grid(const pt_grid_desc* d, void* hip_stream, pt_grid** out) {
     if (e == hipSuccess) e = hipStreamSynchronize(s);
     if (e != hipSuccess) {
         (void)hipGetLastError();
-        free_grid(g);
+        free_grids(g);
         return fail(hip_code(e), "grid upload failed: %s", hipGetErrorString(e));
     }
     if (herr[0] || herr[1] || herr[2] || herr[3]) {
-        free_grid(g);
+        free_grids(g);
         if (herr[0]) return fail(PT_ERR_INVALID_ARG, "a face flow is not finite");
         if (herr[1]) return fail(PT_ERR_INVALID_ARG, "a porosity is not finite and > 0");
         if (herr[2]) return fail(PT_ERR_INVALID_ARG, "a cell flag has unknown bits");
@@ -1125,7 +1153,7 @@ int pt_load_quad_grid(const pt_quad_desc* d, void* hip_stream, pt_grid** out) {
     hipError_t e = grid_memory(g, m.used);
     if (e != hipSuccess) {
         (void)hipGetLastError();
-        free_grid(g);
+        free_grids(g);
         return fail(hip_code(e), "grid allocation failed: %s", hipGetErrorString(e));
     }
     m.base = static_cast<char*>(g->mem);
@@ -1164,11 +1192,11 @@ int pt_load_quad_grid(const pt_quad_desc* d, void* hip_stream, pt_grid** out) {
     if (e == hipSuccess) e = hipStreamSynchronize(s);
     if (e != hipSuccess) {
         (void)hipGetLastError();
-        free_grid(g);
+        free_grids(g);
         return fail(hip_code(e), "grid upload failed: %s", hipGetErrorString(e));
     }
     if (herr[0] || herr[1] || herr[2] || herr[3]) {
-        free_grid(g);
+        free_grids(g);
         if (herr[0]) return fail(PT_ERR_INVALID_ARG, "a subface flow is not finite");
         if (herr[1]) return fail(PT_ERR_INVALID_ARG, "a porosity is not finite and > 0");
         if (herr[2]) return fail(PT_ERR_INVALID_ARG, "a cell flag has unknown bits");
@@ -1468,7 +1496,7 @@ int pt_shutdown(void) {
         if (*reinterpret_cast<uint32_t*>(h) == kGridMagic) {
             pt_grid* g = static_cast<pt_grid*>(h);
             (void)hipSetDevice(g->device);
-            free_grid(g);
+            free_grids(g);
         } else {
             pt_run* r = static_cast<pt_run*>(h);
             (void)hipSetDevice(r->device);
@@ -1495,7 +1523,8 @@ int pt_release(void* h) {
         // no run may still read it; memory whose device reports a fault is not kept
         const bool idle = hipDeviceSynchronize() == hipSuccess;
         int dev = -1;
-        free_grid(g, idle && hipGetDevice(&dev) == hipSuccess && dev == g->device);
+        if (idle && hipGetDevice(&dev) == hipSuccess && dev == g->device) keep_grid(g);
+        else free_grids(g);
         return PT_OK;
     }
     pt_run* r = static_cast<pt_run*>(h);

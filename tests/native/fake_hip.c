@@ -213,6 +213,44 @@ static void reuse(void) {
     CHECK(live[0] == 0 && nlive[0] == 0, "%zu bytes live after the shutdown", live[0]);
 }
 
+/* The limits are a device's own; the oldest blocks leave first. */
+static void limits(void) {
+    const int max_blocks = 8;
+    const size_t max_bytes = (size_t)256 << 20;
+    pt_grid* g[20];
+    for (int q = 0; q < 20; ++q) g[q] = load(1000 * (q + 1));
+    const int in_use = nlive[0];
+    CHECK(in_use == 20, "%d blocks for 20 grids", in_use);
+    for (int q = 0; q < 20; ++q) pt_release(g[q]);
+    CHECK(nlive[0] == max_blocks, "%d blocks kept", nlive[0]);
+    /* a loop over a size that the full pool does not hold finds its own block the second time */
+    pt_release(load(100000));
+    int m = mallocs;
+    for (int q = 0; q < 5; ++q) pt_release(load(100000));
+    CHECK(mallocs == m, "%d allocations in a loop over a new size", mallocs - m);
+    CHECK(nlive[0] == max_blocks, "%d blocks kept", nlive[0]);
+    /* the other device has room of its own */
+    device = 1;
+    for (int q = 0; q < 8; ++q) g[q] = load(1000);
+    for (int q = 0; q < 8; ++q) pt_release(g[q]);
+    CHECK(nlive[0] == max_blocks && nlive[1] == max_blocks, "%d and %d blocks kept", nlive[0], nlive[1]);
+    m = mallocs;
+    for (int q = 0; q < 8; ++q) g[q] = load(1000);
+    CHECK(mallocs == m, "blocks of the device were not taken");
+    for (int q = 0; q < 8; ++q) pt_release(g[q]);
+    device = 0;
+    /* bytes: 100 MB grids, and one above the limit, which leaves the others alone */
+    const int n100 = 100 * 1000 * 1000 / 124;
+    for (int q = 0; q < 4; ++q) g[q] = load(n100);
+    for (int q = 0; q < 4; ++q) pt_release(g[q]);
+    CHECK(live[0] <= max_bytes && live[0] > max_bytes / 2, "%zu bytes kept", live[0]);
+    const size_t kept = live[0];
+    pt_release(load(3 * n100));
+    CHECK(live[0] == kept, "%zu bytes kept, %zu before", live[0], kept);
+    pt_shutdown();
+    CHECK(live[0] == 0 && live[1] == 0, "%zu and %zu bytes live after the shutdown", live[0], live[1]);
+}
+
 /* The default stream while another stream is being captured: the runtime refuses to say whether it is
  * being captured.  The call runs, and does not rely on what an uncertain call left behind. */
 static void capture_refused(void) {
@@ -237,6 +275,7 @@ int main(int argc, char** argv) {
     const char* s = argc > 1 ? argv[1] : "";
     if (!strcmp(s, "run_buffers")) run_buffers();
     else if (!strcmp(s, "reuse")) reuse();
+    else if (!strcmp(s, "limits")) limits();
     else if (!strcmp(s, "capture_refused")) capture_refused();
     else return 2;
     pt_shutdown();

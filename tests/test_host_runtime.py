@@ -2,7 +2,7 @@
 
 tests/native/fake_hip.c defines the HIP calls the library makes and is linked before the runtime, so the
 library's allocations, releases and launches are seen and limited from outside: memory of released grids
-that another allocation needs and its reuse, and calls whose stream the runtime refuses to describe.
+that another allocation needs, its reuse and its limits, and calls that the runtime refuses to describe.
 """
 import os
 import subprocess
@@ -25,7 +25,7 @@ def exe(tmp_path_factory):
     return out
 
 
-@pytest.mark.parametrize("scenario", ["run_buffers", "reuse", "capture_refused"])
+@pytest.mark.parametrize("scenario", ["run_buffers", "reuse", "limits", "capture_refused"])
 def test_host_runtime(exe, scenario):
     r = subprocess.run([exe, scenario], capture_output=True, text=True, timeout=120)
     assert r.returncode == 0 and r.stdout.strip() == "ok", r.stdout[-2000:] + r.stderr[-2000:]
