@@ -472,7 +472,8 @@ def main():
         tuned = tuned_params(wname, precision, wmode) or {}
         sched_id = 1 if schedule == "static" else 2
         if schedule == "auto" and tuned:
-            return tuned, ("static" if tuned.get("schedule") == 1 else "persistent")
+            # an entry with schedule 0 is the library's own launch of a static kernel
+            return tuned, ("persistent" if tuned.get("schedule") == 2 else "static")
         if schedule == "auto":
             return dict(schedule=2), "persistent"
         if tuned.get("schedule") == sched_id:

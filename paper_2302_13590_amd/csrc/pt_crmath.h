@@ -520,7 +520,7 @@ PT_CR_HD double expm1_cr(double x, unsigned* ambiguous) {
 // polynomial (the table-driven method of Tang), with the rounding test of Ziv's strategy.  The result is
 // held as an unnormalised pair h + l with an absolute error bound e that shrinks with the square of the
 // reduced argument, so the sums need no double-double arithmetic: everything beyond the reduced argument's
-// own high part r is below 2^-16 |r| and is summed in double.  Every bound below counts the roundings of
+// own high part r is below 0.52 r^2 and is summed in double.  Every bound below counts the roundings of
 // those sums, each at most 2^-53 of a term no larger than 0.52 p, p = r^2.  What is left undecided goes
 // to the quick phase.  In the table cell next to 0 that is at most 12 |x| (expm1: 10 |x|) of the arguments
 // x; measured, log1p / expm1: 1.4e-2 / 1.3e-2 of 2^-9 < |x| < 2^-8, 8e-4 / 7e-4 of 2^-14 < |x| < 2^-13,
