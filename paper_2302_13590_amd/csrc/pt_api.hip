@@ -651,11 +651,13 @@ int make_plan(const pt_grid* const* grids, int32_t n_grids, const pt_particles* 
         P.grid = (int)std::max<int64_t>(1, (p->n + 15) / 16);
     } else if (P.key.sched == S_STATIC) {
         // Default block.  One wave when the particles give each compute unit at most one (a block
-        // of four would leave compute units idle: 4,096 particles 275 / 286 us), and when each
-        // lane's place is taken eight times or more (no wave waits for its block's slowest: 4e6 with
-        // wells 11.2 / 12.9 ms).  In between four waves, which spread evenly over a compute unit's
-        // SIMDs when the last blocks drain (1e6: 1.97 / 2.14 ms; transient 5e5: 1.47 / 1.57 ms); always
-        // four where every thread holds LDS slots (snapshots, 2e5: 2.14 / 2.85 ms).
+        // of four would leave compute units idle: 16,000 particles on a quadtree 310 / 336 us, mixed
+        // with 60 snapshots 697 / 730, face arrays 398 / 414; at 32,000 mixed endpoints lose by it, 188 /
+        // 181), and when each lane's place is taken eight times or more (no wave waits for its
+        // block's slowest: 4e6 with wells 11.2 / 12.9 ms).  In between four waves, which spread
+        // evenly over a compute unit's SIMDs when the last blocks drain (1e6: 1.97 / 2.14 ms;
+        // transient 5e5: 1.47 / 1.57 ms); always four where every thread holds LDS slots (snapshots,
+        // 2e5: 2.14 / 2.85 ms).
         const bool slots = P.key.out != O_END;
         if (!P.block) P.block = (p->n <= (int64_t)64 * n_cu || (p->n >= 8 * resident && !slots)) ? 64 : 256;
         // a multiple of 8 chunks of blocks: chunks are dealt to the dies round robin

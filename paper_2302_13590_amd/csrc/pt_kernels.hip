@@ -1439,19 +1439,22 @@ __device__ __forceinline__ void finish_fast(Lane<PREC>& L, int32_t st, const Tra
 }
 
 // ---------------------------------------------------------------------------------------------
-// Waves per SIMD the register allocator is asked to fit.  FP64: four (128 VGPRs, a constant of
-// the rare accurate phase in scratch) instead of three at 136 VGPRs -- the fourth wave hides
-// more of the dependent FP64 latency and the record gathers (C2 -9%, C3 -10%); five (96 VGPRs)
-// spill live loop values and are slower.  Mixed: eight for endpoint runs (C3 -5%), six for
-// timeseries and pathlines (C5 -4%; eight spills there).
+// Waves per SIMD the register allocator is asked to fit.  FP64: four (110 to 128 VGPRs, scratch in two
+// quadtree kernels only).  Five (96) spill live loop values: call times of four / five, 1e6 particles 1.93 /
+// 1.99 ms, 6e6 in 64 groups 12.1 / 15.5, 2e5 with 100 snapshots 2.04 / 2.61, 5e5 transient 1.49 / 1.88.
+// Asked for three, the kernels take up to 141: 1 to 2% shorter endpoint runs, 0.53 -> 0.50 ms on the
+// quadtree, but 2.04 -> 2.24 with 100 snapshots.  Mixed: eight for endpoint runs (six: 1e6 particles 0.97 ->
+// 0.95 ms, 5e5 transient 0.76 -> 0.83), six for timeseries and pathlines (eight spill: 2e5 with 100
+// snapshots 1.12 -> 1.41 ms, 2e5 pathlines 0.98 -> 1.23).
 // Rounding mode of the fast kernels: undecided evaluations go to the careful pass.
 constexpr int kFastCr = ptcr::CR_FLAG;
 
 template <int PREC, int OUT>
 constexpr int kWavesStatic = waves_static(PREC, OUT);
-// Persistent kernel: FP64 three (168 VGPRs instead of ~175, a few bytes of rarely used values in
-// scratch: C3 -20%, C2 -13%; four spill 110-230 bytes per lane and are slower); mixed six for
-// endpoint runs (C4 -7%), four otherwise.
+// Persistent kernel: FP64 three (137 to 168 VGPRs).  Four spill 20 to 196 bytes per lane: call times of
+// three / four, 1e6 particles 2.55 / 2.72 ms, 4e6 with wells, ordered, 12.3 / 13.5 and unordered 13.0 /
+// 14.7 (the static kernel: 11.2 ordered, 17.7 unordered), 3e5 on a quadtree 0.84 / 0.99, 2e5 pathlines 1.85 /
+// 2.53.  Mixed six for endpoint runs (1e6: eight 1.42 -> 1.82 ms), four otherwise.
 template <int PREC, int OUT>
 constexpr int kWavesPersistent = PREC == P64 ? 3 : (OUT == O_END ? 6 : 4);
 
@@ -1620,7 +1623,8 @@ k_track_persistent(TrackParams P) {
 // that no face stops.  It pays while its four times as many waves are at most two per SIMD.  Call times
 // against one lane per particle: 1,000 particles on 2,200-step paths 1.66 / 2.54 ms, 10,000 1.72 /
 // 2.56, 30,000 2.38 / 2.66; 4,096 backward 152 / 267 us; 5,000 pathlines 373 / 619 us; 10,000 with
-// 100 snapshots 0.64 / 1.09 ms.
+// 100 snapshots 0.64 / 1.09 ms; near the limit of the rule, at 32,000 particles: pathlines 592 / 672 us, 100
+// snapshots 870 / 1,131, transient 370 / 454, with wells 570 / 717, to the outlet 254 / 289.
 template <int CTRL>
 __device__ __forceinline__ int32_t dpp(int32_t v) {
     return __builtin_amdgcn_update_dpp(v, v, CTRL, 0xf, 0xf, false);
@@ -2014,7 +2018,7 @@ __global__ void __launch_bounds__(1024) k_sort_spread(SortParams S) {
     __shared__ unsigned part[16];
     super_starts(S, at, part);
     __syncthreads();
-    // entries of super-buckets that the tile does not hold are never read
+    // super-buckets that the tile does not hold have no entry in cnt: what is read for them is not used
     for (int q = threadIdx.x; q < S.nsuper; q += blockDim.x) at[q] += S.cnt[(int64_t)blockIdx.x * S.nsuper + q];
     __syncthreads();
     const int64_t base = (int64_t)blockIdx.x * S.tile;

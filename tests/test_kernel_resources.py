@@ -77,3 +77,11 @@ def test_tracking_kernel_occupancy(usage):
     assert len(occ) >= 30, sorted(occ)
     low = {k: o for k, o in occ.items() if o < _waves_floor(k)}
     assert not low, low
+
+
+def test_axes_kernel_resources(usage):
+    """The four-lanes-per-particle kernels are launched with at most two waves per SIMD (128 particles per
+    compute unit); every form holds those two and spills nothing."""
+    axes = {k: v for k, v in usage.items() if "k_track_axes" in k}
+    assert len(axes) == 6, sorted(axes)
+    assert all(v.get("Occupancy", 0) >= 2 and v.get("ScratchSize", 0) == 0 for v in axes.values()), axes
