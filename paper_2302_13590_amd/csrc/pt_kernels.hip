@@ -195,12 +195,14 @@ constexpr double kFilterMargin = 0x1p-15;
 // lanes; for x <= -1/2 the ratio u_e/u_p is formed directly.  Error: ~7 ulp in x, propagated
 // with a factor below 1, ~10 ulp in the quotient, ~6 ulp in D/u_p: below 1.5e-6 relative, a
 // tenth of what the selection margin allows.  The bound needs normal FP32 operands and results;
-// `sure` says that they are: |u_p| >= 2^-70, and the distance D, the logarithm's argument and the
-// estimate at least 2^-50 (so u_e, their product in the ratio form, is at least 2^-120, and
-// |u_p| <= 2^58, since E >= 2^-50 and log1p(x)/x < 70 there).  NaN fails the comparisons.  A
-// subnormal distance or estimate carries an absolute rounding of 2^-149, i.e. any relative error,
-// and a zero distance (a particle already on the face, a zero-time crossing) is decided exactly
-// as well.
+// `sure` says that they are: the distance D and the logarithm's argument q, which have no unit, at least
+// 2^-26, and |u_p| and the estimate, which scale with the unit of time, at least 2^-100 (so u_e = q u_p in
+// the ratio form is at least 2^-126, and |u_p| <= 2^106, since E >= 2^-100 and log1p(x)/x < 70 there).
+// NaN fails the comparisons.  A subnormal distance or estimate carries an absolute rounding of 2^-149,
+// i.e. any relative error, and a zero distance (a particle already on the face, a zero-time crossing) is
+// decided exactly as well.  The bounds share the exponents between the two products: with 2^-50 and
+// 2^-70 (velocities from 1e-21 to 1e15 only) the 1e6-particle field with its flows scaled by 1e-20 or
+// 1e18 took 4.67 ms, every step exact; now, as unscaled, 2.0 ms.
 __device__ __forceinline__ float exit_estimate(double D, double up, double A, double ue, bool& sure) {
     const float upf = (float)up;
     const float Df = (float)D;
@@ -214,7 +216,7 @@ __device__ __forceinline__ float exit_estimate(double D, double up, double A, do
     const float ph = (u == 1.0f) ? 1.0f   // |x| < 2^-24: log1p(x)/x = 1 - x/2 + ...
                                  : (__builtin_amdgcn_logf(q) * 0.693147181f) * __builtin_amdgcn_rcpf(den);
     const float E = rf * ph;
-    sure = (int)(fminf(fabsf(Df), q) >= 0x1p-50f) & (int)(fabsf(upf) >= 0x1p-70f) & (int)(E >= 0x1p-50f);
+    sure = (int)(fminf(fabsf(Df), q) >= 0x1p-26f) & (int)(fabsf(upf) >= 0x1p-100f) & (int)(E >= 0x1p-100f);
     return E;
 }
 
@@ -267,8 +269,8 @@ __device__ __forceinline__ void estimate_exit64(const double (&u1)[3], const dou
 // Correctly rounded exit time of the chosen axis (exit_time64's operations) with the lean phase, for
 // lanes that come with `ok`.  An undecided rounding is repaired in place where waves are full (5% of
 // wave steps, with half the instructions of the general function), or clears `ok` (REPAIR false).
-// The estimates' ranges (u_p in [2^-70, 2^58], D in [2^-50, 1], u_e at least
-// 2^-120 in the ratio form, |x| < 2^128) keep every quotient inside the range of div_by.
+// The estimates' ranges (u_p in [2^-100, 2^106], D in [2^-26, 1], u_e at least
+// 2^-126 in the ratio form, |x| < 2^128) keep every quotient inside the range of div_by.
 // |x| < 2^-60 (zero included) has log1p(x)/x = 1.
 template <int CR, bool REPAIR>
 __device__ __forceinline__ double exit_time64_fast(const Exit64& X, bool& ok, unsigned& amb) {

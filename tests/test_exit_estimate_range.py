@@ -55,10 +55,11 @@ def _exact(D, up, A, ue):
 def _draw(rng, n):
     """Operands of feasible axes on both sides of every threshold: D, u_p, A, u_e."""
     sign = rng.choice([-1.0, 1.0], n)
-    up = sign * 2.0 ** np.where(rng.random(n) < 0.4, rng.uniform(-75, -65, n), rng.uniform(-130, 130, n))
-    D = np.minimum(1.0, 2.0 ** np.where(rng.random(n) < 0.4, rng.uniform(-55, -45, n), rng.uniform(-160, 0.5, n))) * sign
-    # u_e / u_p: strong deceleration (around 2^-50), uniform, acceleration up to where x overflows FP32
-    ratio = 2.0 ** np.choose(rng.integers(0, 4, n), [rng.uniform(-55, -45, n), rng.uniform(-160, 0, n), rng.uniform(-3, 3, n),
+    near_up, near = np.log2(LOW_UP) + rng.uniform(-5, 5, n), np.log2(LOW) + rng.uniform(-5, 5, n)
+    up = sign * 2.0 ** np.where(rng.random(n) < 0.3, near_up, rng.uniform(-130, 130, n))
+    D = np.minimum(1.0, 2.0 ** np.choose(rng.integers(0, 3, n), [near, rng.uniform(-160, 0.5, n), rng.uniform(-20, 0.5, n)])) * sign
+    # u_e / u_p: strong deceleration (around the threshold), uniform, acceleration up to where x overflows FP32
+    ratio = 2.0 ** np.choose(rng.integers(0, 4, n), [np.log2(LOW) + rng.uniform(-5, 5, n), rng.uniform(-160, 0, n), rng.uniform(-3, 3, n),
                                                      rng.uniform(0, 200, n)])
     ratio = np.where(rng.random(n) < 0.1, 1.0 + 2.0 ** rng.uniform(-60, -20, n), ratio)
     with np.errstate(all="ignore"):
@@ -71,6 +72,10 @@ def _draw(rng, n):
 def test_trusted_estimates_and_what_follows_from_them():
     rng = np.random.default_rng(2024)
     trusted = total = 0
+    assert LOW * LOW_UP >= 2.0 ** -126                          # u_e = q u_p is a normal FP32 number
+    # the velocities, in cells per unit of time, of any field in any units: seconds in tight rock and so on
+    assert LOW_UP <= 2.0 ** -100 and LOW_E <= 2.0 ** -100
+    top = 70.0 / LOW_E                                          # D / u_p >= E / 70, D <= 1
     worst = 0.0
     near = 0
     for _ in range(8):
@@ -83,9 +88,9 @@ def test_trusted_estimates_and_what_follows_from_them():
         assert np.isfinite(Es).all()
         worst = max(worst, float(np.abs(Es / dt[sure] - 1.0).max()))
         # what exit_time64_fast's divisions rely on
-        assert np.abs(up[sure]).max() <= 2.0 ** 58 and np.abs(up[sure]).min() >= 2.0 ** -70.01
-        assert np.abs(D[sure]).min() >= 2.0 ** -50.01 and np.abs(D[sure]).max() <= 1.0
-        assert np.abs(ue[sure & ratio]).min() >= 2.0 ** -120.1
+        assert 0.99 * LOW_UP <= np.abs(up[sure]).min() and np.abs(up[sure]).max() <= top <= 2.0 ** 107
+        assert 0.99 * LOW <= np.abs(D[sure]).min() and np.abs(D[sure]).max() <= 1.0
+        assert np.abs(ue[sure & ratio]).min() >= 0.99 * LOW * LOW_UP
         assert np.abs(x[sure]).max() < 2.0 ** 128
         trusted += int(sure.sum())
         total += sure.size
@@ -104,10 +109,10 @@ def test_trusted_estimates_and_what_follows_from_them():
     (0.5, -1.0, 1e38, -1e-45),            # ratio form, u_e below FP32
     (0.5, 1.0, np.inf, np.inf), (0.5, np.inf, np.inf, np.inf), (0.5, np.inf, np.nan, np.inf),
     (0.5, np.nan, 1.0, 1.0), (np.nan, 1.0, 1.0, 1.0), (0.5, 1.0, np.nan, 1.0),
-    (1.0, 2.0 ** -71, 0.0, 2.0 ** -71),   # just below each threshold
-    (2.0 ** -51, 1.0, 0.0, 1.0),
-    (1.0, 1.0, 2.0 ** -51 - 1.0, 2.0 ** -51),
-    (1.0, 2.0 ** 51, 0.0, 2.0 ** 51),
+    (1.0, LOW_UP / 2, 0.0, LOW_UP / 2),   # just below each threshold
+    (LOW / 2, 1.0, 0.0, 1.0),
+    (1.0, 1.0, LOW / 2 - 1.0, LOW / 2),
+    (1.0, 2 / LOW_E, 0.0, 2 / LOW_E),
 ], ids=str)
 def test_never_trusted(D, up, A, ue):
     rng = np.random.default_rng(5)
@@ -116,8 +121,8 @@ def test_never_trusted(D, up, A, ue):
 
 
 @pytest.mark.parametrize("D, up, A, ue", [
-    (1.0, 2.0 ** -69, 0.0, 2.0 ** -69), (2.0 ** -49, 1.0, 0.0, 1.0), (1.0, 1.0, 2.0 ** -49 - 1.0, 2.0 ** -49),
-    (1.0, 2.0 ** 49, 0.0, 2.0 ** 49), (-0.5, -1.0, 0.0, -1.0)], ids=str)
+    (1.0, 2 * LOW_UP, 0.0, 2 * LOW_UP), (2 * LOW, 1.0, 0.0, 1.0), (1.0, 1.0, 2 * LOW - 1.0, 2 * LOW),
+    (1.0, 0.5 / LOW_E, 0.0, 0.5 / LOW_E), (-0.5, -1.0, 0.0, -1.0)], ids=str)
 def test_trusted_just_inside(D, up, A, ue):
     rng = np.random.default_rng(6)
     E, sure, _ = _sure(*(np.array([v], dtype=np.float64) for v in (D, up, A, ue)), rng)
