@@ -195,14 +195,15 @@ constexpr double kFilterMargin = 0x1p-15;
 // lanes; for x <= -1/2 the ratio u_e/u_p is formed directly.  Error: ~7 ulp in x, propagated
 // with a factor below 1, ~10 ulp in the quotient, ~6 ulp in D/u_p: below 1.5e-6 relative, a
 // tenth of what the selection margin allows.  The bound needs normal FP32 operands and results;
-// `sure` says that they are: the distance D and the logarithm's argument q, which have no unit, at least
-// 2^-26, and |u_p| and the estimate, which scale with the unit of time, at least 2^-100 (so u_e = q u_p in
-// the ratio form is at least 2^-126, and |u_p| <= 2^106, since E >= 2^-100 and log1p(x)/x < 70 there).
-// NaN fails the comparisons.  A subnormal distance or estimate carries an absolute rounding of 2^-149,
-// i.e. any relative error, and a zero distance (a particle already on the face, a zero-time crossing) is
-// decided exactly as well.  The bounds share the exponents between the two products: with 2^-50 and
-// 2^-70 (velocities from 1e-21 to 1e15 only) the 1e6-particle field with its flows scaled by 1e-20 or
-// 1e18 took 4.67 ms, every step exact; now, as unscaled, 2.0 ms.
+// `sure` says that they are.  m, the smaller of the distance D and the logarithm's argument q (both at
+// most 1 or no matter), and m |u_p| are at least 2^-120: so are D, q, |u_p| and, in the ratio form, u_e =
+// q u_p.  The estimate is at least 2^-100, so |u_p| <= 2^107 (D <= 1, log1p(x)/x < 84 there).  NaN fails
+// the comparisons: fminf passes it by, but the estimate of a NaN operand is one.  A subnormal distance or
+// estimate carries an absolute rounding of 2^-149, i.e. any relative error, and a zero distance (a
+// particle already on the face, a zero-time crossing) is decided exactly as well.  Every step outside the
+// range is exact: bounds that narrow it to velocities of 2^-70 .. 2^56 cost a 1e6-particle field with its
+// flows scaled by 1e-20 or 1e18 4.67 ms instead of 2.0, and a floor of 2^-26 under D and q instead of the
+// product cost a field whose velocities jump by 1e12 from face to face 2.2 ms instead of 1.2.
 __device__ __forceinline__ float exit_estimate(double D, double up, double A, double ue, bool& sure) {
     const float upf = (float)up;
     const float Df = (float)D;
@@ -216,7 +217,8 @@ __device__ __forceinline__ float exit_estimate(double D, double up, double A, do
     const float ph = (u == 1.0f) ? 1.0f   // |x| < 2^-24: log1p(x)/x = 1 - x/2 + ...
                                  : (__builtin_amdgcn_logf(q) * 0.693147181f) * __builtin_amdgcn_rcpf(den);
     const float E = rf * ph;
-    sure = (int)(fminf(fabsf(Df), q) >= 0x1p-26f) & (int)(fabsf(upf) >= 0x1p-100f) & (int)(E >= 0x1p-100f);
+    const float m = fminf(fabsf(Df), q);
+    sure = (int)(fminf(m, m * fabsf(upf)) >= 0x1p-120f) & (int)(E >= 0x1p-100f);
     return E;
 }
 
@@ -269,8 +271,8 @@ __device__ __forceinline__ void estimate_exit64(const double (&u1)[3], const dou
 // Correctly rounded exit time of the chosen axis (exit_time64's operations) with the lean phase, for
 // lanes that come with `ok`.  An undecided rounding is repaired in place where waves are full (5% of
 // wave steps, with half the instructions of the general function), or clears `ok` (REPAIR false).
-// The estimates' ranges (u_p in [2^-100, 2^106], D in [2^-26, 1], u_e at least
-// 2^-126 in the ratio form, |x| < 2^128) keep every quotient inside the range of div_by.
+// The estimates' ranges (u_p in [2^-120, 2^107], D in [2^-120, 1], u_e at least
+// 2^-120 in the ratio form, |x| < 2^128) keep every quotient inside the range of div_by.
 // |x| < 2^-60 (zero included) has log1p(x)/x = 1.
 template <int CR, bool REPAIR>
 __device__ __forceinline__ double exit_time64_fast(const Exit64& X, bool& ok, unsigned& amb) {

@@ -1,8 +1,8 @@
 """When the FP64 kernels trust their FP32 exit-time estimates (CPU).
 
 An estimate is bounded by 1.5e-6 only while its FP32 operands and results are normal numbers, so the kernel
-takes it as sure only inside ranges that it tests with three comparisons: |u_p| from below, the smaller of
-the distance and the logarithm's argument from below, the estimate from below.  The upper bounds follow from
+takes it as sure only inside ranges that it tests with two comparisons: m, the smaller of the distance and the
+logarithm's argument, and m |u_p| from below, and the estimate from below.  Every other bound follows from
 these, and the divisions of the exit time evaluated afterwards rely on them.  The thresholds are read from
 the kernel's source; the estimate is emulated in float32 with the hardware's reciprocal and logarithm moved
 by up to the 2 ulp measured for them.
@@ -20,15 +20,15 @@ SOURCE = os.path.join(ROOT, "paper_2302_13590_amd", "csrc", "pt_kernels.hip")
 
 
 def _thresholds():
-    """(min of |D| and q, |u_p|, E) of the kernel's rule; fails when the rule has another form."""
+    """(min of m and m |u_p|, E) of the kernel's rule; fails when the rule has another form."""
     src = open(SOURCE).read()
-    m = re.search(r"sure = \(int\)\(fminf\(fabsf\(Df\), q\) >= (\S+)f\) & \(int\)\(fabsf\(upf\) >= (\S+)f\) & "
-                  r"\(int\)\(E >= (\S+)f\);", src)
+    m = re.search(r"const float m = fminf\(fabsf\(Df\), q\);\s+"
+                  r"sure = \(int\)\(fminf\(m, m \* fabsf\(upf\)\) >= (\S+)f\) & \(int\)\(E >= (\S+)f\);", src)
     assert m, "exit_estimate no longer decides `sure` in the form that this test emulates"
     return tuple(float.fromhex(v) for v in m.groups())
 
 
-LOW, LOW_UP, LOW_E = _thresholds()
+LOW, LOW_E = _thresholds()
 
 
 def _sure(D, up, A, ue, rng):
@@ -41,7 +41,8 @@ def _sure(D, up, A, ue, rng):
         ratio = ~(xf > F(-0.5))
         q = np.where(ratio, (ue.astype(F) * rup).astype(F), (F(1.0) + xf).astype(F))
         # fminf passes a NaN by, comparisons with one fail
-        sure = (np.fmin(np.abs(Df), q) >= F(LOW)) & (np.abs(upf) >= F(LOW_UP)) & (E >= F(LOW_E))
+        m = np.fmin(np.abs(Df), q)
+        sure = (np.fmin(m, (m * np.abs(upf)).astype(F)) >= F(LOW)) & (E >= F(LOW_E))
     return E, sure, ratio
 
 
@@ -55,11 +56,11 @@ def _exact(D, up, A, ue):
 def _draw(rng, n):
     """Operands of feasible axes on both sides of every threshold: D, u_p, A, u_e."""
     sign = rng.choice([-1.0, 1.0], n)
-    near_up, near = np.log2(LOW_UP) + rng.uniform(-5, 5, n), np.log2(LOW) + rng.uniform(-5, 5, n)
-    up = sign * 2.0 ** np.where(rng.random(n) < 0.3, near_up, rng.uniform(-130, 130, n))
+    up = sign * 2.0 ** np.where(rng.random(n) < 0.5, rng.uniform(-130, 130, n), rng.uniform(-40, 40, n))
+    near = np.log2(LOW) - np.minimum(np.log2(np.abs(up)), 0.0) + rng.uniform(-5, 5, n)   # m or m |u_p| at the threshold
     D = np.minimum(1.0, 2.0 ** np.choose(rng.integers(0, 3, n), [near, rng.uniform(-160, 0.5, n), rng.uniform(-20, 0.5, n)])) * sign
     # u_e / u_p: strong deceleration (around the threshold), uniform, acceleration up to where x overflows FP32
-    ratio = 2.0 ** np.choose(rng.integers(0, 4, n), [np.log2(LOW) + rng.uniform(-5, 5, n), rng.uniform(-160, 0, n), rng.uniform(-3, 3, n),
+    ratio = 2.0 ** np.choose(rng.integers(0, 4, n), [np.minimum(near, 0.0), rng.uniform(-160, 0, n), rng.uniform(-3, 3, n),
                                                      rng.uniform(0, 200, n)])
     ratio = np.where(rng.random(n) < 0.1, 1.0 + 2.0 ** rng.uniform(-60, -20, n), ratio)
     with np.errstate(all="ignore"):
@@ -72,10 +73,8 @@ def _draw(rng, n):
 def test_trusted_estimates_and_what_follows_from_them():
     rng = np.random.default_rng(2024)
     trusted = total = 0
-    assert LOW * LOW_UP >= 2.0 ** -126                          # u_e = q u_p is a normal FP32 number
-    # the velocities, in cells per unit of time, of any field in any units: seconds in tight rock and so on
-    assert LOW_UP <= 2.0 ** -100 and LOW_E <= 2.0 ** -100
-    top = 70.0 / LOW_E                                          # D / u_p >= E / 70, D <= 1
+    assert LOW >= 2.0 ** -126                                   # D, q, u_p and u_e = q u_p: normal FP32 numbers
+    top = 84.0 / LOW_E                                          # D / u_p >= E / 84, D <= 1
     worst = 0.0
     near = 0
     for _ in range(8):
@@ -88,13 +87,13 @@ def test_trusted_estimates_and_what_follows_from_them():
         assert np.isfinite(Es).all()
         worst = max(worst, float(np.abs(Es / dt[sure] - 1.0).max()))
         # what exit_time64_fast's divisions rely on
-        assert 0.99 * LOW_UP <= np.abs(up[sure]).min() and np.abs(up[sure]).max() <= top <= 2.0 ** 107
+        assert 0.99 * LOW <= np.abs(up[sure]).min() and np.abs(up[sure]).max() <= top <= 2.0 ** 107
         assert 0.99 * LOW <= np.abs(D[sure]).min() and np.abs(D[sure]).max() <= 1.0
-        assert np.abs(ue[sure & ratio]).min() >= 0.99 * LOW * LOW_UP
+        assert np.abs(ue[sure & ratio]).min() >= 0.99 * LOW
         assert np.abs(x[sure]).max() < 2.0 ** 128
         trusted += int(sure.sum())
         total += sure.size
-        near += int((np.abs(np.log2(np.abs(up[sure]) / LOW_UP)) < 1).sum() + (np.log2(np.abs(D[sure]) / LOW) < 1).sum())
+        near += int((np.log2(np.abs(D[sure]) * np.minimum(1.0, np.abs(up[sure])) / LOW) < 1).sum())
     assert worst < BOUND, worst
     assert total // 20 < trusted < total // 2 and near > 1000   # both verdicts, and next to the thresholds
 
@@ -109,7 +108,7 @@ def test_trusted_estimates_and_what_follows_from_them():
     (0.5, -1.0, 1e38, -1e-45),            # ratio form, u_e below FP32
     (0.5, 1.0, np.inf, np.inf), (0.5, np.inf, np.inf, np.inf), (0.5, np.inf, np.nan, np.inf),
     (0.5, np.nan, 1.0, 1.0), (np.nan, 1.0, 1.0, 1.0), (0.5, 1.0, np.nan, 1.0),
-    (1.0, LOW_UP / 2, 0.0, LOW_UP / 2),   # just below each threshold
+    (1.0, LOW / 2, 0.0, LOW / 2),         # just below each threshold
     (LOW / 2, 1.0, 0.0, 1.0),
     (1.0, 1.0, LOW / 2 - 1.0, LOW / 2),
     (1.0, 2 / LOW_E, 0.0, 2 / LOW_E),
@@ -121,9 +120,23 @@ def test_never_trusted(D, up, A, ue):
 
 
 @pytest.mark.parametrize("D, up, A, ue", [
-    (1.0, 2 * LOW_UP, 0.0, 2 * LOW_UP), (2 * LOW, 1.0, 0.0, 1.0), (1.0, 1.0, 2 * LOW - 1.0, 2 * LOW),
+    (1.0, 2 * LOW, 0.0, 2 * LOW), (2 * LOW_E, 1.0, 0.0, 1.0), (1.0, 1.0, -1.0, 2 * LOW),
     (1.0, 0.5 / LOW_E, 0.0, 0.5 / LOW_E), (-0.5, -1.0, 0.0, -1.0)], ids=str)
 def test_trusted_just_inside(D, up, A, ue):
     rng = np.random.default_rng(6)
     E, sure, _ = _sure(*(np.array([v], dtype=np.float64) for v in (D, up, A, ue)), rng)
     assert sure[0], E
+
+
+@pytest.mark.parametrize("jump, scale", [(1.0, 1e-27), (1e-6, 1e-24), (1e-12, 1e-20), (1e-12, 1e-9), (1e-12, 1.0),
+                                         (1e-12, 1e14), (1e-12, 1e22)])
+def test_trusted_in_any_unit_of_time(jump, scale):
+    """Ordinary steps, also towards a face that is 1e12 times slower, are trusted whatever unit the
+    velocities are in: nothing but the margin sends them to three exact exit times."""
+    rng = np.random.default_rng(7)
+    n = 20_000
+    up = scale * rng.uniform(0.01, 10.0, n)
+    D = rng.uniform(1e-6, 1.0, n)
+    ue = up * jump * rng.uniform(0.5, 1.0, n)
+    E, sure, _ = _sure(D, up, (ue - up) / D, ue, rng)
+    assert sure.all()
