@@ -1125,8 +1125,8 @@ __device__ __forceinline__ void hash_cell(unsigned long long& h, int32_t c) {
 // chain when it is not.  So the common path is straight-line: estimates, the record of the next
 // cell (its gather hides behind the arithmetic), one lean exit time, two lean advances; undecided
 // lanes repair their values in branches (an axis' advance in ~6% of the wave steps: small A tau, whose
-// expm1 has few bits to spare).  1e6 particles through a 100x100x10 field: 686 -> 458 VALU instructions
-// per 64 crossings, kernel 2.93 -> 1.84 ms; repairing the logarithm and each expm1 in place, instead
+// expm1 has few bits to spare).  1e6 particles through a 100x100x10 field: 686 -> 462 VALU instructions
+// per 64 crossings, kernel 2.93 -> 1.90 ms; repairing the logarithm and each expm1 in place, instead
 // of the whole exit time or both advances, took the last 3%.
 template <int PREC, int LAYOUT, int OUT, bool BATCHED, int CR>
 __device__ __forceinline__ int32_t track_step(Lane<PREC>& L, const TrackParams& P, const double* snap,
