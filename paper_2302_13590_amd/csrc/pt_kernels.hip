@@ -1698,20 +1698,29 @@ __global__ void __launch_bounds__(kBlock) k_track_axes(TrackParams P) {
             bool ok = (int)(low >= 0x1p-100) & (int)(high <= 0x1p100);
             unsigned undecided = 0u;
             double dt = exit_time64_fast<CR, false>(ex, ok, undecided);
+            int32_t face = 4 * own + (pos ? 2 : 0);   // bit 0: an exit time of -0.0
             if (feasible && !ok) {
                 dt = exit_core64<CR>(ex.Aw, ex.upw, ex.D, ex.ue, undecided);
                 dt = dt < dinf() ? dt : dinf();   // a time that is NaN is never the earliest
+                face |= (int32_t)(ptcr::bits_of(dt) >> 63);   // zeros arise here only
+                dt = __builtin_fabs(dt);
             }
             dt = feasible ? dt : dinf();
-            // the earliest axis, ties to the lowest: face 2 axis + high of the smallest key
+            // the earliest axis, ties to the lowest: face 2 axis + high of the smallest key, bits 1 to 3.  The
+            // step's time is that of this axis with its sign, -0.0 to a face at 0 and +0.0 to one at 1, which
+            // shows in the other axes' coordinates of -0.0 and in a time of -0.0; the minimum of both zeros
+            // need not be it.  (The sign in the key: 10,000 particles on 2,200-step paths 1,723 -> 1,740 us;
+            // as a branch on a time of zero 1,801.)
             const double d1 = dpp<kNext>(dt), d2 = dpp<kOther>(dt);
-            const double dtw = __builtin_fmin(__builtin_fmin(dt, d1), d2);
-            if (undecided && dt <= dtw * (1.0 + kFilterMargin)) L.amb += undecided;
-            const int32_t key = (dt == dtw) ? 2 * own + (pos ? 1 : 0) : 7;
-            const int32_t f = min(min(key, dpp<kNext>(key)), dpp<kOther>(key));
-            const bool none = !(dtw < dinf());
-            const int32_t axis = f >> 1;
-            const bool hi = f & 1;
+            const double dtm = __builtin_fmin(__builtin_fmin(dt, d1), d2);
+            if (undecided && dt <= dtm * (1.0 + kFilterMargin)) L.amb += undecided;
+            const int32_t key = (dt == dtm) ? face : 14;
+            const int32_t fs = min(min(key, dpp<kNext>(key)), dpp<kOther>(key));
+            const int32_t f = fs >> 1;
+            const double dtw = ptcr::of_bits(ptcr::bits_of(dtm) | ((uint64_t)(uint32_t)fs << 63));
+            const bool none = !(dtm < dinf());
+            const int32_t axis = fs >> 2;
+            const bool hi = fs & 2;
             const bool mine = !none && own == axis;
 
             const int32_t stride = axis == 0 ? 1 : (axis == 1 ? G.nx : G.plane);

@@ -7,6 +7,8 @@ oracle evaluates the formulas as they are written, so every kernel form must agr
 The same holds for the sign of a zero coordinate, and for what counts as a recheck: an evaluation whose
 value the track does not use hands no particle to the careful pass.
 """
+import itertools
+
 import numpy as np
 import pytest
 
@@ -103,6 +105,27 @@ def test_negative_zero_coordinates(pt):
     g.qx[:] = 0.0
     g.qy[:] = 0.0
     _check(g, p, "negative zero, no flow", t_max=1.0)
+
+
+def test_sign_of_a_zero_exit_time(pt):
+    """Axes that leave at once, in a tie: a face at 0 is reached in -0.0, one at 1 in +0.0.  The step takes the
+    time of the axis it leaves through, the lowest, and its sign decides that of a -0.0 on the other axes."""
+    g = H.box_grid(3, 3, 3, 1.0, 1.0, 1.0, porosity=1.0)
+    loc = np.array(list(itertools.product((0.0, -0.0, 0.5, 1.0), repeat=3)))
+    for signs in itertools.product((1.0, -1.0), repeat=3):
+        for q, s, a in zip((g.qx, g.qy, g.qz), signs, (0, 0, 0.125)):
+            q[:] = s
+            q[:, :, 1:] += a * s
+        for t in (0.0, -0.0):
+            p = H.particles([13] * len(loc), *loc.T)
+            p.t[:] = t
+            for steps in (1, 50):
+                r = O.track(g, p, max_steps=steps)
+                for f in FORMS:
+                    out = gpu_track([g], p, max_steps=steps, **f)
+                    compare(out, r, label="%s %s %s" % (signs, t, f))
+                    for k in ("xi", "eta", "zeta", "t"):
+                        assert _same_sign(out[k], getattr(r, k)), (signs, t, steps, f, k)
 
 
 def _unit(q):
